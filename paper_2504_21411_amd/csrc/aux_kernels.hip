@@ -303,6 +303,36 @@ static __device__ void build_Rc_part(int block, int nblocks, const float *__rest
   }
 }
 
+// bounds[k][0][si] = largest, bounds[k][1][si] = least R[si][sj] over the targets sj: one wave per
+// 16 sources, four lanes sharing a source.
+static __device__ void build_bounds_part(int block, int nblocks, const float *__restrict__ Rt,
+                                         float *__restrict__ bounds, int S, int SP, int K) {
+  const int lane = threadIdx.x & 63;
+  const int per = (SP + 15) / 16; // waves per matrix
+  for (long long x = (long long)block * 4 + (threadIdx.x >> 6); x < (long long)K * per;
+       x += (long long)nblocks * 4) {
+    const long long k = x / per;
+    const int i = (int)(x % per) * 16 + (lane & 15);
+    const float *col = Rt + k * SP * SP + (i < SP ? i : SP - 1);
+    float hi = 0.0f, lo = GS_INF;
+#pragma unroll 16
+    for (int j = lane >> 4; j < S; j += 4) {
+      const float v = col[(size_t)j * SP];
+      hi = __builtin_fmaxf(hi, v);
+      lo = __builtin_fminf(lo, v);
+    }
+#pragma unroll
+    for (int d = 16; d <= 32; d <<= 1) {
+      hi = __builtin_fmaxf(hi, __shfl_xor(hi, d, kWave));
+      lo = __builtin_fminf(lo, __shfl_xor(lo, d, kWave));
+    }
+    if (lane < 16 && i < SP) {
+      bounds[(k * 2) * SP + i] = hi;
+      bounds[(k * 2 + 1) * SP + i] = lo;
+    }
+  }
+}
+
 // r_class[s] = number of layout changes along desc[0..s] (one block, serial prefix over S
 // <= 1024 entries by a scan in shared memory).
 __global__ __launch_bounds__(1024) void k_layout_classes(const int32_t *__restrict__ desc, int S,
@@ -1256,7 +1286,7 @@ __global__ __launch_bounds__(256) void k_bin_unit(
     int32_t *__restrict__ status_acc, int L, int SP, int M, int enable, int all_rows,
     const float *__restrict__ Rt, const int32_t *__restrict__ cmeta,
     const int32_t *__restrict__ cstart, float *__restrict__ Rc, int K, int NC,
-    unsigned *__restrict__ epoch) {
+    unsigned *__restrict__ epoch, float *__restrict__ bounds, int S) {
   const int block = (int)blockIdx.x;
   // The solve counter the class kernel's flags are stamped with (see k_dp_class_fronts):
   // advanced here, on the device, so that a captured and replayed solve advances it as well.
@@ -1274,6 +1304,8 @@ __global__ __launch_bounds__(256) void k_bin_unit(
   if (block < B)
     bin_unit_part(block, Oq, budget, budget0, unit, minO, lowsum, topsum, status, status_acc, L,
                   SP, M, enable, all_rows);
+  else if (bounds)
+    build_bounds_part(block - B, (int)gridDim.x - B, Rt, bounds, S, SP, K);
   else
     build_Rc_part(block - B, (int)gridDim.x - B, Rt, cmeta, cstart, Rc, SP, K, NC);
 }
@@ -1286,7 +1318,9 @@ void launch_prepare(const Shape &s, const float *T, const int32_t *O, const floa
   const unsigned nb_tables = (unsigned)((waves + 3) / 4);
   // r_class: the class promise is checked, and the class table built, in the same launches
   const unsigned nb_classes = r_class ? blocks_for((long long)s.K * s.S * s.S, 256, 4096) : 0;
-  const unsigned nb_rc = r_class ? blocks_for((long long)s.K * s.NC * s.NC, 256, 4096) : 0;
+  const unsigned nb_rc = r_class    ? blocks_for((long long)s.K * s.NC * s.NC, 256, 4096)
+                         : w.bounds ? blocks_for((long long)s.K * ((s.SP + 15) / 16), 4, 4096)
+                                    : 0;
   hipLaunchKernelGGL(k_prepare, dim3(nb_tables + nb_classes), dim3(256), 0, st, (int)nb_tables, T,
                      O, R, r_index, budget, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.minO,
                      w.status_acc, s.B, s.L, s.S, s.M, s.K, s.SP, r_class, w.cmeta, w.cstart,
@@ -1294,7 +1328,7 @@ void launch_prepare(const Shape &s, const float *T, const int32_t *O, const floa
   hipLaunchKernelGGL(k_bin_unit, dim3((unsigned)s.B + nb_rc), dim3(256), 0, st, s.B, w.Oq,
                      w.budget, w.budget0, w.unit, w.minO, w.lowsum, w.topsum, w.status,
                      w.status_acc, s.L, s.SP, s.M, compress_bins ? 1 : 0, all_rows ? 1 : 0, w.Rt,
-                     w.cmeta, w.cstart, w.Rc, s.K, s.NC, w.epoch);
+                     w.cmeta, w.cstart, w.Rc, s.K, s.NC, w.epoch, w.bounds, s.S);
 }
 
 void launch_layout_classes(const int32_t *desc, int S, int32_t *r_class, int32_t *count_out,

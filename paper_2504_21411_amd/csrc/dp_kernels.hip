@@ -505,6 +505,354 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
 }
 
 // ---------------------------------------------------------------------------------------
+// General transition table with bounds (k_dp_bound, reported as the tile-streaming family
+// k_dp_wide that it refines): most source strategies cannot be the
+// best of any target, and a bound that costs a few instructions per source says which.
+//
+// For a wave's targets let hi[i] and lo[i] be the largest and the least R[i][j] over them.
+// For a row, U = min_i fl(C[i] + hi[i]) is at least every target's minimum, and a source with
+// fl(C[i] + lo[i]) > U is, because the rounded add is monotone, strictly larger than the
+// minimum for every target: leaving it out changes neither the minimum nor the lowest index
+// that attains it.  A wave scans, in ascending order, the sources that some row of its 64
+// needs.  How many remain depends on the tables: layer times that differ by more than the
+// transition costs leave 10 to 18 of 44 and 15 to 20 of 96, and fewer the fewer targets share
+// a wave (cost model on 1024 devices: 60 of 242 with 16 targets, 100 with 32, 200 with all),
+// while costs that dwarf the differences leave all; then the wave takes the plain scan.
+//
+// A workgroup owns a 64-row tile in LDS ([si][64], one row of +inf behind it); a wave owns JW
+// targets and keeps their running results in registers.
+//   short scan  eight listed sources a step.  C[r][i] + R[i][j] is one V_MFMA_F32_4X4X1 per
+//     source and four targets: the accumulator input holds C of the lane's row four times,
+//     B = 1, and A holds the transition values, so each result is the same single rounded sum
+//     as a vector add gives (infinities and denormals included).  CBSZ = 4 and ABID broadcast
+//     one of A's sixteen blocks: 64 gathered transition values sit in one register and none
+//     has to be a scalar operand, which a gather could not feed.  Then compare, select, minimum.
+//   plain scan  all sources in chunks of eight with scalar transition values; eight adds and
+//     four three-input minima (the running minimum among their operands) per chunk, the first
+//     chunk that attains the minimum is looked at again (see k_dp_tile).
+//
+// Bound by the vector ALU where little is left out, else by the latency of a tile's steps
+// (tile, bounds, list, gather; four waves per SIMD at 103 to 128 registers).  Whole searches,
+// before / after: 8 instances, 128 layers, 96 strategies, 16385 rows 5.11 / 3.86 ms; 4, 48, 242,
+// 4097 4.66 / 3.10 ms; 7, 17, 30, 778 155 / 137 us.  One bound over all targets is shared by the
+// workgroup's waves (each looks at the sources it fetched, 4 instructions a source); with more
+// than 128 strategies each wave bounds its own targets (6 a source, and their table columns).
+// ---------------------------------------------------------------------------------------
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+// sum[v] = cc[v] + (value v of block AB of a)
+template <int AB>
+static __device__ __forceinline__ float4_t mat_add(float a, const float4_t &cc) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, 1.0f, cc, 4, AB, 0);
+}
+// all four registers = c
+static __device__ __forceinline__ float4_t mat_spread(float c) {
+  const float4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(1.0f, c, z, 0, 0, 0);
+}
+
+// Four targets (half H of a group of eight) against eight listed sources id[].
+template <int H, bool WITH_BP>
+static __device__ __forceinline__ void mat_step(float *m, int *g, float a, const float4_t (&cc)[8],
+                                                const int (&id)[8]) {
+  const float4_t d[8] = {mat_add<8 * H + 0>(a, cc[0]), mat_add<8 * H + 1>(a, cc[1]),
+                         mat_add<8 * H + 2>(a, cc[2]), mat_add<8 * H + 3>(a, cc[3]),
+                         mat_add<8 * H + 4>(a, cc[4]), mat_add<8 * H + 5>(a, cc[5]),
+                         mat_add<8 * H + 6>(a, cc[6]), mat_add<8 * H + 7>(a, cc[7])};
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    float mv = m[4 * H + v];
+    int gv = g[4 * H + v];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (WITH_BP) gv = d[k][v] < mv ? id[k] : gv;
+      mv = __builtin_fminf(mv, d[k][v]);
+    }
+    m[4 * H + v] = mv;
+    g[4 * H + v] = gv;
+  }
+}
+
+template <int NW, int JW, bool WITH_BP, bool GROUPED>
+__global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(3))) void k_dp_bound(
+    const float *__restrict__ src, float *__restrict__ dst, uint8_t *__restrict__ bp,
+    const float *__restrict__ Tq, const int32_t *__restrict__ Oq,
+    const float *__restrict__ Rt, const float *__restrict__ bounds,
+    const int32_t *__restrict__ ridx,
+    const int32_t *__restrict__ budget, const int32_t *__restrict__ topsum,
+    const int32_t *__restrict__ lowsum, int B, int L, int S, int SP, int l, int pitch) {
+  // [8 np + 1][64], then [NW][8 np + 8] uint16 lists, and unless GROUPED [NW][64] partial
+  // bounds and [NW] masks
+  extern __shared__ float tile[];
+  constexpr int NU = (NW * JW + 63) / 64; // 64-source words
+  const int b = blockIdx.x % B;
+  const int js = wave_uniform(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int tile_start = (int)(blockIdx.x / B) * kWave;
+  const int E = budget[b];
+  if (tile_start > E) return; // whole workgroup
+  const int np = (S + 15) / 16 * 2; // steps of eight sources, a whole number of pairs
+  float *part = tile + (8 * np + 1) * kWave; // (not there when GROUPED)
+  unsigned *masks = reinterpret_cast<unsigned *>(part + NW * kWave);
+  uint16_t *list = (GROUPED ? reinterpret_cast<uint16_t *>(part)
+                            : reinterpret_cast<uint16_t *>(masks + NW)) +
+                   js * (8 * np + 8);
+
+  const int row = tile_start + lane;
+  const bool valid = row <= E;
+  const int bl = b * L + l;
+  const int low = lowsum[bl - 1]; // rows below it are +inf in the previous plane
+  const int top = E - topsum[bl]; // rows above it lead to no result
+  const bool compute = tile_start <= top && tile_start + kWave > low; // uniform
+  const size_t plane_off = (size_t)b * S * pitch;
+  const float *__restrict__ srcb = src + plane_off;
+  float *__restrict__ dstb = dst + plane_off;
+  uint8_t *__restrict__ bpb = WITH_BP ? bp + plane_off : nullptr;
+  const float *__restrict__ rk = Rt + (size_t)ridx[bl] * SP * SP;
+  const float *__restrict__ trow = Tq + (size_t)bl * SP;
+  const int32_t *__restrict__ orow = Oq + (size_t)bl * SP;
+  const int jbeg = js * JW;
+  const int jend = jbeg + JW < S ? jbeg + JW : S; // (<= jbeg: a wave without targets)
+
+  if (compute) {
+    // sources JW js ...: JW loads of a wave in flight; padding is +inf
+    const uint32_t rowc = (uint32_t)(valid ? row : E);
+    float stage[JW];
+#pragma unroll
+    for (int u = 0; u < JW; ++u) {
+      const int i = jbeg + u;
+      stage[u] = (srcb + (size_t)(i < S ? i : S - 1) * pitch)[rowc];
+    }
+#pragma unroll
+    for (int u = 0; u < JW; ++u) {
+      const int i = jbeg + u;
+      stage[u] = (i < S && valid) ? stage[u] : GS_INF;
+      if (i < 8 * np) tile[i * kWave + lane] = stage[u];
+    }
+    if (js == 0) tile[8 * np * kWave + lane] = GS_INF;
+    // rows whose result nobody reads need no source
+    const bool idle = row < low || row > top;
+    int n = 0; // listed sources
+    if constexpr (GROUPED) {
+      // lane i: bounds of sources i, i + 64, ... over this wave's targets
+      float hi[NU], lo[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        hi[u] = 0.0f;
+        lo[u] = GS_INF;
+        const int i = 64 * u + lane;
+        const float *col = rk + (i < SP ? i : SP - 1);
+#pragma unroll
+        for (int x = 0; x < JW; ++x) {
+          const int j = jbeg + x < S ? jbeg + x : S - 1; // (the last target again)
+          const float v = col[(size_t)j * SP];
+          hi[u] = __builtin_fmaxf(hi[u], v);
+          lo[u] = __builtin_fminf(lo[u], v);
+        }
+      }
+      __syncthreads();
+      float bound = GS_INF;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) { // (padding rows are +inf)
+          const float *tq = tile + (64 * u + i0) * kWave + lane;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const float h = __builtin_bit_cast(
+                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, hi[u]), i0 + k));
+            bound = __builtin_fminf(bound, tq[k * kWave] + h);
+          }
+        }
+      bound = idle ? -1.0f : bound;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        unsigned long long word = 0;
+        for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) {
+          const float *tq = tile + (64 * u + i0) * kWave + lane;
+          unsigned bits = 0;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const float h = __builtin_bit_cast(
+                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lo[u]), i0 + k));
+            bits |= __builtin_amdgcn_ballot_w64(tq[k * kWave] + h <= bound) != 0 ? 1u << k : 0u;
+          }
+          word |= (unsigned long long)bits << i0;
+        }
+        if (64 * u + 64 > S) word &= 64 * u < S ? ~0ull >> (64 * u + 64 - S) : 0ull;
+        const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
+        if (word >> lane & 1) list[at] = (uint16_t)(64 * u + lane);
+        n += __builtin_popcountll(word);
+      }
+    } else {
+      // one bound for all targets, each wave looking at the sources it fetched; the table
+      // holds hi[SP], lo[SP] of this transition matrix
+      const float *__restrict__ hi = bounds + (size_t)ridx[bl] * 2 * SP + jbeg;
+      const float *__restrict__ lo = hi + SP;
+      float bound = GS_INF;
+#pragma unroll
+      for (int u = 0; u < JW; ++u) bound = __builtin_fminf(bound, stage[u] + hi[u]);
+      if constexpr (NW > 1) {
+        part[js * kWave + lane] = bound;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NW; ++u) bound = __builtin_fminf(bound, part[u * kWave + lane]);
+      }
+      bound = idle ? -1.0f : bound;
+      unsigned bits = 0;
+#pragma unroll
+      for (int u = 0; u < JW; ++u)
+        bits |= __builtin_amdgcn_ballot_w64(stage[u] + lo[u] <= bound) != 0 ? 1u << u : 0u;
+      if (lane == 0) masks[js] = bits;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int i = 64 * u + lane;
+        const bool on = i < S && (masks[i < NW * JW ? i / JW : 0] >> (i % JW) & 1u) != 0;
+        const unsigned long long word = __builtin_amdgcn_ballot_w64(on);
+        const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
+        if (on) list[at] = (uint16_t)i;
+        n += __builtin_popcountll(word);
+      }
+    }
+    const int steps = (n + 7) / 8;
+    if (n + lane < 8 * steps) list[n + lane] = (uint16_t)(8 * np); // the row of +inf
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (jbeg < S) {
+      auto store = [&](int j, float v, int from) {
+        const int eo = row + orow[j];
+        if (row >= low && eo <= E) {
+          (dstb + (size_t)j * pitch)[(uint32_t)eo] = v + trow[j];
+          if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)from;
+        }
+      };
+      // A listed source costs about three times a source of the plain scan (compare and select
+      // for each, and the adds do not overlap the minima: 22 cycles for four sums and their
+      // minima where either alone takes 8), twice without the argmin; a plain scan pays 30
+      // instructions a target for the chunk's second look, or 90 sources' worth over ten.
+      const bool brief = WITH_BP ? 10 * n <= 3 * S + 90 : 2 * n <= S + 8; // wave-uniform
+      if (brief) {
+        float m[JW];
+        int g[JW];
+#pragma unroll
+        for (int x = 0; x < JW; ++x) {
+          m[x] = GS_INF;
+          g[x] = 0;
+        }
+        // A operand of targets 8x .. 8x+7 against a step's eight sources: lane 4 (8 h + k) + i
+        // holds target 8x + 4h + i, source k of the step
+        const float *ra[JW / 8];
+#pragma unroll
+        for (int x = 0; x < JW / 8; ++x) {
+          const int j = jbeg + 8 * x + 4 * (lane >> 5) + (lane & 3);
+          ra[x] = rk + (size_t)(j < SP ? j : SP - 1) * SP;
+        }
+        const int k_own = (lane >> 2) & 7;
+        float a[JW / 8]; // (steps > 0: a row that is read needs a source)
+        {
+          const int own = steps > 0 ? list[k_own] : 0;
+#pragma unroll
+          for (int x = 0; x < JW / 8; ++x) a[x] = ra[x][own < SP ? own : SP - 1];
+        }
+        for (int p = 0; p < steps; ++p) {
+          // the next step's values are requested while these are used
+          const int own = list[8 * (p + 1 < steps ? p + 1 : p) + k_own];
+          float an[JW / 8];
+#pragma unroll
+          for (int x = 0; x < JW / 8; ++x) an[x] = ra[x][own < SP ? own : SP - 1];
+          int id[8];
+          float4_t cc[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            id[k] = wave_uniform(list[8 * p + k]);
+            cc[k] = mat_spread(tile[id[k] * kWave + lane]);
+          }
+#pragma unroll
+          for (int x = 0; x < JW / 8; ++x) {
+            mat_step<0, WITH_BP>(m + 8 * x, g + 8 * x, a[x], cc, id);
+            mat_step<1, WITH_BP>(m + 8 * x, g + 8 * x, a[x], cc, id);
+            a[x] = an[x];
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < JW; ++x)
+          if (jbeg + x < S) store(jbeg + x, m[x], g[x]);
+      } else {
+        // JB targets a pass as in k_dp_wide: 16 (8 for four targets) scalar transition values
+        // of each, the next ones requested while these are used (SP is a multiple of 16)
+        constexpr int JB = WITH_BP ? 2 : 4;
+        constexpr int W = WITH_BP ? 16 : 8;
+        typedef float vec_t __attribute__((ext_vector_type(W)));
+        const int nq = (S + W - 1) / W;
+        for (int j0 = jbeg; j0 < jend; j0 += JB) {
+          const float *__restrict__ rc[JB];
+          float mx[JB];
+          int gx[JB];
+          vec_t r[JB];
+#pragma unroll
+          for (int x = 0; x < JB; ++x) {
+            rc[x] = rk + (size_t)(j0 + x < jend ? j0 + x : j0) * SP;
+            mx[x] = GS_INF;
+            gx[x] = 0;
+            r[x] = *reinterpret_cast<const vec_t *>(rc[x]);
+          }
+          for (int q = 0; q < nq; ++q) {
+            const int qn = q + 1 < nq ? q + 1 : q;
+            vec_t rn[JB];
+#pragma unroll
+            for (int x = 0; x < JB; ++x) rn[x] = *reinterpret_cast<const vec_t *>(rc[x] + W * qn);
+#pragma unroll
+            for (int h = 0; h < W / 8; ++h) {
+              const float *tq = tile + (W * q + 8 * h) * kWave + lane;
+              float c[8];
+#pragma unroll
+              for (int k = 0; k < 8; ++k) c[k] = tq[k * kWave];
+#pragma unroll
+              for (int x = 0; x < JB; ++x) {
+                float mn = mx[x];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) mn = __builtin_fminf(mn, c[k] + r[x][8 * h + k]);
+                if (WITH_BP) gx[x] = mn < mx[x] ? W / 8 * q + h : gx[x];
+                mx[x] = mn;
+              }
+            }
+#pragma unroll
+            for (int x = 0; x < JB; ++x) r[x] = rn[x];
+          }
+#pragma unroll
+          for (int x = 0; x < JB; ++x) {
+            const int j = j0 + x;
+            if (j >= jend) break;
+            if (WITH_BP) {
+              const float *__restrict__ rg = rc[x] + 8 * gx[x];
+              const float *tg = tile + 8 * gx[x] * kWave + lane;
+              const float4 fa = *reinterpret_cast<const float4 *>(rg);
+              const float4 fb = *reinterpret_cast<const float4 *>(rg + 4);
+              const float rr[8] = {fa.x, fa.y, fa.z, fa.w, fb.x, fb.y, fb.z, fb.w};
+              int kk = 7; // (one of the chunk's sums is the minimum)
+#pragma unroll
+              for (int k = 6; k >= 0; --k) kk = tg[k * kWave] + rr[k] == mx[x] ? k : kk;
+              gx[x] = 8 * gx[x] + kk;
+            }
+            store(j, mx[x], gx[x]);
+          }
+        }
+      }
+    }
+  }
+  // +inf prefix of the target rows that no computed source row reaches
+  for (int j = jbeg; j < jend; ++j) {
+    const int below = orow[j] + low;
+    if (tile_start < below && valid && row < below) {
+      (dstb + (size_t)j * pitch)[(uint32_t)row] = GS_INF;
+      if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)row] = 0;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // The same tile kernel for strategy counts beyond the register-tiled sizes (129 .. 1024):
 // the tile stays in LDS and level 1 streams it from there, JB target strategies per pass
 // so that every LDS read serves JB relaxations (4 / JB bytes of LDS traffic per relaxation; the
@@ -2105,12 +2453,82 @@ static void launch_wide(const Shape &s, const Workspace &w, int l, const float *
   else launch_wide_as<uint8_t, true>(s, w, l, src, dst, bp_l, st);
 }
 
+template <int NW, int JW, bool GROUPED>
+static void launch_bound_as(const Shape &s, const Workspace &w, int l, const float *src, float *dst,
+                            void *bp_l, hipStream_t st) {
+  const long long tiles = (s.M + 1 + kWave - 1) / kWave;
+  const dim3 grid((unsigned)(tiles * s.B)), block(NW * kWave);
+  const size_t n8 = (size_t)(s.S + 15) / 16 * 16;
+  const size_t lds = sizeof(float) * ((n8 + 1) * kWave + (GROUPED ? 0 : NW * kWave + NW)) +
+                     sizeof(uint16_t) * NW * (n8 + 8);
+  if (lds > 64 * 1024)
+    lds_opt_in(bp_l ? (const void *)k_dp_bound<NW, JW, true, GROUPED>
+                    : (const void *)k_dp_bound<NW, JW, false, GROUPED>,
+               lds, s.grants);
+  if (bp_l)
+    hipLaunchKernelGGL((k_dp_bound<NW, JW, true, GROUPED>), grid, block, lds, st, src, dst,
+                       (uint8_t *)bp_l, w.Tq, w.Oq, w.Rt, w.bounds, w.ridx, w.budget, w.topsum,
+                       w.lowsum, s.B, s.L, s.S, s.SP, l, s.pitch);
+  else
+    hipLaunchKernelGGL((k_dp_bound<NW, JW, false, GROUPED>), grid, block, lds, st, src, dst,
+                       (uint8_t *)nullptr, w.Tq, w.Oq, w.Rt, w.bounds, w.ridx, w.budget, w.topsum,
+                       w.lowsum, s.B, s.L, s.S, s.SP, l, s.pitch);
+}
+// Which shapes take the bounded kernel by themselves, and in how many waves per tile.  Measured
+// against the kernels below over 12 layers, layer times of 1 to 10 and transition costs of up
+// to 1 / 2 / 4 (how far the bounds reach depends on that ratio; new / old time, the last of
+// the three with little left out):
+//   with backpointers  S = 44, 16 and 128 tiles 0.73 / 0.78 / 0.94 and 0.78 / 0.90 / 0.99, 520
+//     tiles 0.95 / 1.06 / 1.18 (not taken); S = 64, 520 tiles 0.75 / 0.87 / 1.00, 4 K tiles 1.17 at
+//     worst (not taken); S = 96, 4 K tiles 0.61 / 0.79 / 1.05, the 64-device cost model 0.76;
+//     S = 128, 520 tiles 0.59 / 0.77 / 1.05; S = 162 0.67 / 0.80 / 1.17 (not taken); S = 242,
+//     128 tiles 0.47 / 0.61 / 0.86, the 1024-device cost model 0.65, 2 K tiles 1.38 at worst
+//   without            S = 44, 128 tiles 0.82 / 0.84 / 0.96; S = 64, 4 K tiles 0.75 / 0.84 / 0.94;
+//     S = 96, 4 K tiles 0.61 / 0.65 / 0.80; S = 128 0.55 / 0.65 / 0.85; S = 162 0.63 / 0.70 / 0.80;
+//     S = 242, 128 tiles 0.45 / 0.51 / 0.63, 2 K tiles 0.71 / 0.81 / 1.00
+// Few targets per wave while the batch has few tiles (a front is one wave's length then), more
+// when the set-up of each wave counts.
+static bool bound_pays(const Shape &s, bool with_bp) {
+  const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
+  switch (s.SP) {
+    case 32: case 48: return tiles <= 256;
+    case 64: return !with_bp || tiles <= 1024;
+    case 96: return true;
+    case 128: return !with_bp || tiles <= 1024;
+    default: break;
+  }
+  return s.SP > 128 && (!with_bp || (s.SP > 192 && tiles <= 1024));
+}
+
+#define GS_BOUND(NW, JW, GR) return launch_bound_as<NW, JW, GR>(s, w, l, src, dst, bp_l, st)
+static void launch_bound(const Shape &s, const Workspace &w, int l, const float *src, float *dst,
+                         void *bp_l, hipStream_t st) {
+  const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
+  switch (s.SP) {
+    case 32: GS_BOUND(4, 8, false);
+    case 48: GS_BOUND(6, 8, false);
+    case 64: if (tiles <= 1024) GS_BOUND(8, 8, false); GS_BOUND(4, 16, false);
+    case 96: if (tiles <= 1024) GS_BOUND(12, 8, false); GS_BOUND(4, 24, false);
+    case 128: if (tiles <= 256 && bp_l) GS_BOUND(16, 8, false); GS_BOUND(8, 16, false);
+    default: break;
+  }
+  // (one bound per wave: with many strategies a bound over all targets is loose)
+  if (s.SP <= 192) { if (tiles <= 1024) GS_BOUND(12, 16, true); GS_BOUND(8, 24, true); }
+  GS_BOUND(16, 16, true);
+}
+#undef GS_BOUND
+
 const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const float *src,
                             float *dst, void *bp_l, ForwardKernel which, hipStream_t st) {
   const bool force_generic = which == ForwardKernel::Generic;
   const int blocks_per_instance = (s.M + 1 + kRowsPerBlock - 1) / kRowsPerBlock;
   const dim3 grid((unsigned)((size_t)blocks_per_instance * s.B));
   const int tsp = tuned_sp_for(s.S);
+  if (which == ForwardKernel::Auto && w.bounds && s.SP % 16 == 0 && s.SP >= 32 &&
+      (s.tune.kernel == 4 || (s.tune.kernel == 0 && bound_pays(s, bp_l != nullptr)))) {
+    launch_bound(s, w, l, src, dst, bp_l, st);
+    return "k_dp_wide"; // (a form of it)
+  }
   // Which register-tiled kernel: measured on MI355X, the LDS-staged two-level kernel wins
   // from 48 padded strategies up when backpointers are wanted (its argmin costs about 2.3
   // instead of 4 vector instructions per relaxation) and for 48..64 without them; the

@@ -323,6 +323,8 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
   w.cstart = reinterpret_cast<int32_t *>(base + y.cstart);
   w.cls = reinterpret_cast<int32_t *>(base + y.cls);
   w.Rc = reinterpret_cast<float *>(base + y.Rc);
+  // (2 SP <= 512 floats per matrix, in the room of 32 x 32 or more)
+  w.bounds = !p->r_class && s.S > 24 && s.S <= 256 && s.L > 1 ? w.Rc : nullptr;
   w.maxfit = reinterpret_cast<int32_t *>(base + y.maxfit);
   w.stop = reinterpret_cast<unsigned *>(base + y.stop);
   w.epoch = nullptr;

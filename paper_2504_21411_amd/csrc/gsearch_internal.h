@@ -17,7 +17,7 @@ constexpr int kMaxClasses = 64;    // most transition classes a solve can exploi
 // A context reads them once from the environment when it is created (GSEARCH_<NAME>) and
 // gsearch_set_knob changes them afterwards; nothing in the library reads the environment later.
 struct Tuning {
-  int kernel = 0;          // 1 push, 2 tile, 3 wide: force that general forward kernel
+  int kernel = 0;          // 1 push, 2 tile, 3 wide, 4 bound: force that general forward kernel
   int small = -1;          // 0 / 1: the one-launch kernel for small instances never / wherever it fits
   int jsplit = 0;          // waves per tile
   int waves_per_block = 0; // push kernel: waves per workgroup (1..4)
@@ -95,6 +95,8 @@ struct Workspace {
   int32_t *cls;      // [SP]         class of strategy s (0 for the padding)
   float *Rc;         // [K][NC][NC]  Rc[k][cj][ci] = R between the classes'
                      //              first strategies, +inf for padding classes
+  float *bounds;     // [K][2][SP]   without r_class, in Rc's place: largest and least
+                     //              R[si][.] over the targets (null: not filled)
   // Several layer fronts per launch of the class kernel (see k_dp_class_fronts):
   int32_t *maxfit;   // [B][L]       largest O[b][l][s] that fits the budget at all (0: none)
   unsigned *stop;    // one word: a bounded wait gave up somewhere in this solve

@@ -1417,3 +1417,37 @@ def test_general_kernels_random_sweep(gs, oracle_mod):
             assert_same(got, ref, w, f"sweep {case} S={S} flags={flags:#x} groups={g}")
             if curve is not None:
                 assert_curve(oracle_mod, curve, w, f"sweep {case} flags={flags:#x}")
+
+
+# strategy counts at the edges of the bounded kernel's forms: last wave with one target, full
+# and half-filled steps of eight, one and several 64-source words
+@pytest.mark.parametrize("S", [25, 32, 33, 44, 48, 49, 64, 65, 96, 97, 128, 129, 162, 192, 193, 256])
+@pytest.mark.parametrize("flags", [0, 0x4, 0x1])
+def test_bounded_kernel(gs, oracle_mod, S, flags):
+    """k_dp_bound leaves out sources that cannot win: transition costs from far below the layer
+    times (nearly all left out) to far above (none), coarse values (ties), forbidden
+    transitions, budgets that end inside a tile, memories that leave no plan.  Exact."""
+    _, runner = gs
+    for case, (M, r, coarse) in enumerate([(63, 0.5, False), (64, 3.0, True), (200, 2.0, False),
+                                           (300, 40.0, False), (130, 0.0, True)]):
+        rng = np.random.RandomState(100 * S + case)
+        w = random_tables(f"bound{S}_{case}", 3, 4, S, M, K=2, seed=700 + S + case,
+                          budget=np.array([M, max(1, M // 2), M // 7], np.int32))
+        w.R *= np.float32(r / 2.0)
+        if coarse:
+            w.T, w.R = np.ceil(w.T).astype(np.float32), np.floor(w.R).astype(np.float32)
+        if case == 2:
+            w.R[rng.rand(*w.R.shape) < 0.3] = np.inf
+            w.O[2] = M + 1                         # an instance without any plan
+        if case == 3:
+            w.O[0, 1] = 0
+            w.R[0, :, S // 2] = np.inf             # a strategy that nothing may precede
+        ref = oracle_batch(oracle_mod, w)
+        with runner.make_context(w, flags=flags) as ctx:
+            ctx.gsearch_set_knob("kernel", 4)
+            ctx.gsearch_set_knob("small", 0)
+            got = runner.to_numpy(runner.run_step(ctx, runner.DeviceWorkload(w), backtrace="all"))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert_same(got, ref, w, f"flags={flags}")
+            if case == 2:
+                assert_curve(oracle_mod, ctx.gsearch_budget_curve().cpu().numpy(), w)
