@@ -42,7 +42,8 @@ def ops_per_relaxation(kernel: str, mode: str, S: int) -> float:
     kernels): add, compare, two selects.  Two-level argmin (tile kernel): per chunk of
     eight candidates eight adds, four minimum instructions, one compare and two selects
     (15/8), plus the second look at one chunk per target state (8 adds, 8 compares,
-    8 selects = 24 per S relaxations).
+    8 selects = 24 per S relaxations).  The bounded form that is reported as k_dp_wide leaves
+    sources out, depending on the tables; it is priced as if it scanned them all.
     """
     if mode == "nobp":
         return 1.5

@@ -234,8 +234,8 @@ int gsearch_instance_groups(gsearch_ctx *ctx);
 /* Tuning knobs: overrides of the launch heuristics, for sweeps and tests; results never depend
  * on them.  A context takes their initial values from the environment variables
  * GSEARCH_<NAME IN CAPITALS> when it is created (the library reads the environment nowhere
- * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide: general forward
- * kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
+ * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide, 4 the
+ * bounded form of wide: general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
  * "jsplit" (waves per tile), "waves_per_block", "row_groups", "streams" (instance groups),
  * "fronts" (class kernel: layer fronts per launch, 2..64; 0 or 1: one launch per front; -1, the
  * default: 64 wherever that form can run, i.e. a batch that is a multiple of 8 or has 64 instances
