@@ -42,12 +42,12 @@ def ops_per_relaxation(kernel: str, mode: str, S: int) -> float:
     kernels): add, compare, two selects.  Two-level argmin (tile kernel): per chunk of
     eight candidates eight adds, four minimum instructions, one compare and two selects
     (15/8), plus the second look at one chunk per target state (8 adds, 8 compares,
-    8 selects = 24 per S relaxations).  The bounded form that is reported as k_dp_wide leaves
-    sources out, depending on the tables; it is priced as if it scanned them all.
+    8 selects = 24 per S relaxations).  k_dp_bound leaves sources out, depending on
+    the tables; it is priced as if it scanned them all.
     """
     if mode == "nobp":
         return 1.5
-    if kernel in ("k_dp_tile", "k_dp_wide"):
+    if kernel in ("k_dp_tile", "k_dp_wide", "k_dp_bound"):
         return 15.0 / 8.0 + 24.0 / S
     return 4.0
 
@@ -241,7 +241,8 @@ def main():
             upper = np.maximum(rows - top[:, 1:], 0)          # useful source rows of front l
             active = np.maximum(upper - np.minimum(skipped, upper), 0)
             executed = float(active.sum()) / float((rows * (w.L - 1)).sum())
-            if not kernel.startswith(("k_dp_push", "k_dp_tile", "k_dp_wide", "k_dp_class")):
+            if not kernel.startswith(("k_dp_push", "k_dp_tile", "k_dp_wide", "k_dp_bound",
+                                      "k_dp_class")):
                 executed = 1.0
             n_class = int(out["n_class"].cpu()[0]) if "n_class" in out else None
             computed = float(active.sum()) / (w.L - 1)

@@ -234,8 +234,8 @@ int gsearch_instance_groups(gsearch_ctx *ctx);
 /* Tuning knobs: overrides of the launch heuristics, for sweeps and tests; results never depend
  * on them.  A context takes their initial values from the environment variables
  * GSEARCH_<NAME IN CAPITALS> when it is created (the library reads the environment nowhere
- * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide, 4 the
- * bounded form of wide: general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
+ * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide, 4 bound:
+ * general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
  * "jsplit" (waves per tile), "waves_per_block", "row_groups", "streams" (instance groups),
  * "fronts" (class kernel: layer fronts per launch, 2..64; 0 or 1: one launch per front; -1, the
  * default: 64 wherever that form can run, i.e. a batch that is a multiple of 8 or has 64 instances
@@ -268,9 +268,8 @@ int gsearch_get_knob(gsearch_ctx *ctx, const char *name, int *value);
 int gsearch_set_profiling(gsearch_ctx *ctx, int enable);
 int gsearch_forward_ms(gsearch_ctx *ctx, float *host_ms);
 /* Name of the forward kernel the most recent solve launched for its layer fronts
- * ("k_dp_class_fronts", "k_dp_class", "k_dp_tile", "k_dp_wide", "k_dp_push", "k_dp_generic" or
- * "k_dp_small"; "" before any
- * solve; "k_dp_class_fronts" also when its slow stand-in did the work, which only the device
+ * ("k_dp_class_fronts", "k_dp_class", "k_dp_tile", "k_dp_wide", "k_dp_bound", "k_dp_push",
+ * "k_dp_generic" or "k_dp_small"; "" before any solve; "k_dp_class_fronts" also when its slow stand-in did the work, which only the device
  * knows).  Static string. */
 const char *gsearch_forward_kernel(gsearch_ctx *ctx);
 

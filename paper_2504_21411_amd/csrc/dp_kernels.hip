@@ -505,9 +505,8 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
 }
 
 // ---------------------------------------------------------------------------------------
-// General transition table with bounds (k_dp_bound, reported as the tile-streaming family
-// k_dp_wide that it refines): most source strategies cannot be the
-// best of any target, and a bound that costs a few instructions per source says which.
+// General transition table with bounds (k_dp_bound): most source strategies cannot be the best
+// of any target, and a bound that costs a few instructions per source says which.
 //
 // For a wave's targets let hi[i] and lo[i] be the largest and the least R[i][j] over them.
 // For a row, U = min_i fl(C[i] + hi[i]) is at least every target's minimum, and a source with
@@ -2527,7 +2526,7 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
   if (which == ForwardKernel::Auto && w.bounds && s.SP % 16 == 0 && s.SP >= 32 &&
       (s.tune.kernel == 4 || (s.tune.kernel == 0 && bound_pays(s, bp_l != nullptr)))) {
     launch_bound(s, w, l, src, dst, bp_l, st);
-    return "k_dp_wide"; // (a form of it)
+    return "k_dp_bound";
   }
   // Which register-tiled kernel: measured on MI355X, the LDS-staged two-level kernel wins
   // from 48 padded strategies up when backpointers are wanted (its argmin costs about 2.3

@@ -347,7 +347,7 @@ def test_config3_large_dense_full_size(gs, oracle_mod):
     # (the class kernel with 64 layer fronts per launch, its default here, and with one)
     for flags, classes, kernel in ((0, True, "k_dp_class_fronts"), (0x4, True, "k_dp_class_fronts"),
                                    (0, True, "k_dp_class"), (0x4, True, "k_dp_class"),
-                                   (0, False, "k_dp_wide"), (0x4, False, "k_dp_wide")):
+                                   (0, False, "k_dp_bound"), (0x4, False, "k_dp_bound")):
         with runner.make_context(w, flags=flags) as ctx:
             ctx.gsearch_set_knob("fronts", -1 if kernel.endswith("fronts") else 0)
             got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all", classes=classes))
@@ -448,7 +448,7 @@ def test_profiled_table_builder_matches_oracle_and_solves(gs, oracle_mod):
 
 def test_profiling_entry_points(gs):
     binding, runner = gs
-    w = random_tables("timing", 4, 6, 96, 6000, seed=91)       # 376 tiles: the LDS-streamed kernel's range
+    w = random_tables("timing", 4, 6, 96, 6000, seed=91)       # 376 tiles: the bounded kernel's range
     dw = runner.DeviceWorkload(w)
     with runner.make_context(w) as ctx:
         assert ctx.gsearch_forward_kernel() == ""
@@ -459,7 +459,7 @@ def test_profiling_entry_points(gs):
         ctx.gsearch_set_profiling(True)
         runner.run_step(ctx, dw, backtrace=None)
         assert 0.0 < ctx.gsearch_forward_ms() < 1000.0
-        assert ctx.gsearch_forward_kernel() == "k_dp_wide"
+        assert ctx.gsearch_forward_kernel() == "k_dp_bound"
     small = random_tables("timing_small", 1, 5, 12, 100, seed=92)
     with runner.make_context(small) as ctx:
         runner.run_step(ctx, runner.DeviceWorkload(small), backtrace=None)
@@ -1045,7 +1045,7 @@ def test_model_configs_without_classes_use_the_general_kernels(gs, oracle_mod, i
     ref = oracle_batch(oracle_mod, w, T, O, R)
     a = runner.solve_workload(w, classes=True)
     b = runner.solve_workload(w, classes=False)
-    assert a["forward_kernel"].startswith("k_dp_class") and b["forward_kernel"] in ("k_dp_tile", "k_dp_wide")
+    assert a["forward_kernel"].startswith("k_dp_class") and b["forward_kernel"] in ("k_dp_tile", "k_dp_bound")
     assert_same(a, ref, w, "classes")
     assert_same(b, ref, w, "general")
 
@@ -1448,6 +1448,7 @@ def test_bounded_kernel(gs, oracle_mod, S, flags):
             ctx.gsearch_set_knob("small", 0)
             got = runner.to_numpy(runner.run_step(ctx, runner.DeviceWorkload(w), backtrace="all"))
             got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_bound"
             assert_same(got, ref, w, f"flags={flags}")
             if case == 2:
                 assert_curve(oracle_mod, ctx.gsearch_budget_curve().cpu().numpy(), w)
