@@ -2499,6 +2499,16 @@ static bool bound_pays(const Shape &s, bool with_bp) {
   return s.SP > 128 && (!with_bp || (s.SP > 192 && tiles <= 1024));
 }
 
+// Whether a solve of this shape without transition classes runs the bounded kernel.  The knob
+// "kernel" = 4 asks for it wherever it has a form, 1 to 3 for another kernel.
+bool bound_applies(const Shape &s, bool with_bp) {
+  if (s.S <= 24 || s.S > 256) return false;
+  if (s.tune.kernel >= 1 && s.tune.kernel <= 4) return s.tune.kernel == 4;
+  return bound_pays(s, with_bp);
+}
+// The forms with one bound for all targets read it from a table.
+bool bound_needs_table(const Shape &s) { return s.SP <= 128; }
+
 #define GS_BOUND(NW, JW, GR) return launch_bound_as<NW, JW, GR>(s, w, l, src, dst, bp_l, st)
 static void launch_bound(const Shape &s, const Workspace &w, int l, const float *src, float *dst,
                          void *bp_l, hipStream_t st) {
@@ -2523,8 +2533,7 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
   const int blocks_per_instance = (s.M + 1 + kRowsPerBlock - 1) / kRowsPerBlock;
   const dim3 grid((unsigned)((size_t)blocks_per_instance * s.B));
   const int tsp = tuned_sp_for(s.S);
-  if (which == ForwardKernel::Auto && w.bounds && s.SP % 16 == 0 && s.SP >= 32 &&
-      (s.tune.kernel == 4 || (s.tune.kernel == 0 && bound_pays(s, bp_l != nullptr)))) {
+  if (w.bounded) {
     launch_bound(s, w, l, src, dst, bp_l, st);
     return "k_dp_bound";
   }

@@ -323,8 +323,6 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
   w.cstart = reinterpret_cast<int32_t *>(base + y.cstart);
   w.cls = reinterpret_cast<int32_t *>(base + y.cls);
   w.Rc = reinterpret_cast<float *>(base + y.Rc);
-  // (2 SP <= 512 floats per matrix, in the room of 32 x 32 or more)
-  w.bounds = !p->r_class && s.S > 24 && s.S <= 256 && s.L > 1 ? w.Rc : nullptr;
   w.maxfit = reinterpret_cast<int32_t *>(base + y.maxfit);
   w.stop = reinterpret_cast<unsigned *>(base + y.stop);
   w.epoch = nullptr;
@@ -339,7 +337,6 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
   ctx->solved = false;
   ctx->forward_kernel = ""; // (a solve of one layer launches no forward kernel)
   ctx->shape = s;
-  ctx->ws = w;
 
   const size_t pe = gs::plane_elems(s);
   const bool keep = keeps_all_planes(c.flags);
@@ -348,6 +345,14 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
   if (c.flags & GSEARCH_FLAG_FORCE_GENERIC) which = gs::ForwardKernel::Generic;
   else if (c.flags & GSEARCH_FLAG_FORCE_PUSH) which = gs::ForwardKernel::Push;
   else if (c.flags & GSEARCH_FLAG_FORCE_TILE) which = gs::ForwardKernel::Tile;
+
+  // One launch for all fronts of a small instance; else, with nothing known about R, the
+  // bounded kernel where it applies.  Its table (2 SP <= 256 floats per matrix) takes the room
+  // of the class table (32 x 32 floats or more).
+  const bool small = which == gs::ForwardKernel::Auto && gs::small_path_applies(s, with_bp);
+  w.bounded = which == gs::ForwardKernel::Auto && s.L > 1 && !p->r_class && !small &&
+              gs::bound_applies(s, with_bp);
+  w.bounds = w.bounded && gs::bound_needs_table(s) ? w.Rc : nullptr;
 
   // Transition classes: checked whenever the caller states them, exploited by the class
   // kernel when no particular kernel is forced and the shape has a register-tiled size.
@@ -369,7 +374,7 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
   int cur = 0;
   ctx->timed = false;
   const bool timing = ctx->profiling && s.L > 1;
-  if (which == gs::ForwardKernel::Auto && !use_classes && gs::small_path_applies(s, with_bp)) {
+  if (small && !use_classes) {
     // latency path: layer 0 and every layer front in one launch, planes in LDS
     cur = keep ? s.L - 1 : ((s.L - 1) & 1);
     if (timing && hipEventRecord(ctx->ev_begin, st) != hipSuccess) return GSEARCH_ERR_HIP;

@@ -97,6 +97,7 @@ struct Workspace {
                      //              first strategies, +inf for padding classes
   float *bounds;     // [K][2][SP]   without r_class, in Rc's place: largest and least
                      //              R[si][.] over the targets (null: not filled)
+  int bounded;       // 1: the layer fronts run on k_dp_bound
   // Several layer fronts per launch of the class kernel (see k_dp_class_fronts):
   int32_t *maxfit;   // [B][L]       largest O[b][l][s] that fits the budget at all (0: none)
   unsigned *stop;    // one word: a bounded wait gave up somewhere in this solve
@@ -153,6 +154,11 @@ enum class ForwardKernel { Auto, Generic, Push, Tile };
 // Returns the name of the kernel it launched.
 const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const float *src,
                             float *dst, void *bp_l, ForwardKernel which, hipStream_t st);
+// Whether k_dp_bound runs a solve without transition classes and with no kernel forced by a
+// flag (Workspace::bounded is set then), and whether its form reads the table
+// Workspace::bounds (which is built for no other solve).
+bool bound_applies(const Shape &s, bool with_bp);
+bool bound_needs_table(const Shape &s);
 // Single-launch forward pass for small instances (includes layer 0); see dp_kernels.hip.
 bool small_path_applies(const Shape &s, bool with_bp);
 void launch_dp_small(const Shape &s, const Workspace &w, bool keep_all, int last_plane,

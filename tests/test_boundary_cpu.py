@@ -201,3 +201,46 @@ def test_product_package_never_touches_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text, f
                 assert "liboracle" not in text, f
+
+
+# ---- which solves run the bounded kernel (host rule; internal C++ functions of the library) ----
+
+class _Shape(ctypes.Structure):
+    """gs::Shape of csrc/gsearch_internal.h: sizes and pitches, the knobs, a pointer."""
+    _fields_ = ([(n, ctypes.c_int) for n in ("B", "L", "S", "M", "K", "SP", "pitch", "bp16", "Bc",
+                                             "NC")]
+                + [(n, ctypes.c_int) for n in ("kernel", "small", "jsplit", "waves_per_block",
+                                               "row_groups", "streams", "fronts", "front_tiles",
+                                               "spin_limit", "hold_flags")]
+                + [("grants", ctypes.c_void_p)])
+
+
+def _bound_rule(lib, B, S, M, with_bp, kernel=0):
+    class_sp_for = lib._ZN2gs12class_sp_forEi
+    applies = lib._ZN2gs13bound_appliesERKNS_5ShapeEb
+    table = lib._ZN2gs17bound_needs_tableERKNS_5ShapeE
+    applies.restype = table.restype = ctypes.c_bool
+    s = _Shape(B=B, L=4, S=S, M=M, K=1, SP=class_sp_for(S) or (S + 15) // 16 * 16, Bc=B, NC=32,
+               pitch=(M + 64) // 64 * 64, bp16=int(S > 256), kernel=kernel, small=-1, fronts=-1)
+    return applies(ctypes.byref(s), ctypes.c_bool(with_bp)), table(ctypes.byref(s))
+
+
+def test_bounds_are_for_solves_that_use_them(lib):
+    """A kernel forced by the knob needs no bounds, nor does a form that bounds per wave, nor a
+    shape that the rule refuses; knob values without a kernel of their own choose as 0 does."""
+    seen = set()
+    for S in (8, 24, 25, 30, 44, 64, 80, 96, 128, 129, 162, 192, 200, 256, 257, 1024):
+        for B, M in ((1, 100), (4, 1000), (8, 4095), (64, 4095), (256, 4096)):
+            for with_bp in (False, True):
+                use, table = _bound_rule(lib, B, S, M, with_bp)
+                seen.add((use, table))
+                assert table == (S <= 128)
+                assert not use or 25 <= S <= 256
+                for kernel in (1, 2, 3):
+                    assert not _bound_rule(lib, B, S, M, with_bp, kernel)[0]
+                assert _bound_rule(lib, B, S, M, with_bp, 4)[0] == (25 <= S <= 256)
+                for kernel in (-1, 5, 64):
+                    assert _bound_rule(lib, B, S, M, with_bp, kernel)[0] == use
+    assert len(seen) == 4
+    # encoder-decoder batch: the shorter scan saves less than its set-up costs
+    assert not _bound_rule(lib, 256, 44, 4096, True)[0]

@@ -1452,3 +1452,19 @@ def test_bounded_kernel(gs, oracle_mod, S, flags):
             assert_same(got, ref, w, f"flags={flags}")
             if case == 2:
                 assert_curve(oracle_mod, ctx.gsearch_budget_curve().cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("S,M,B", [(30, 1000, 1), (44, 1000, 2), (96, 1000, 1), (200, 500, 2)])
+def test_kernel_knob_without_meaning_is_the_heuristic(gs, S, M, B):
+    """Values of the knob "kernel" that name no kernel choose as 0 does."""
+    _, runner = gs
+    w = random_tables(f"knob{S}", B, 3, S, M, seed=S)
+    dw = runner.DeviceWorkload(w)
+    names = []
+    for value in (0, -1, 5, 64):
+        with runner.make_context(w) as ctx:
+            ctx.gsearch_set_knob("kernel", value)
+            ctx.gsearch_set_knob("small", 0)
+            runner.run_step(ctx, dw, backtrace=None)
+            names.append(ctx.gsearch_forward_kernel())
+    assert names == ["k_dp_bound"] * 4, names
