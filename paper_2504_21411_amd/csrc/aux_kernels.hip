@@ -1286,8 +1286,10 @@ __global__ __launch_bounds__(256) void k_bin_unit(
     int32_t *__restrict__ status_acc, int L, int SP, int M, int enable, int all_rows,
     const float *__restrict__ Rt, const int32_t *__restrict__ cmeta,
     const int32_t *__restrict__ cstart, float *__restrict__ Rc, int K, int NC,
-    unsigned *__restrict__ epoch, float *__restrict__ bounds, int S) {
+    unsigned *__restrict__ epoch, float *__restrict__ bounds, int32_t *__restrict__ votes, int S) {
   const int block = (int)blockIdx.x;
+  if (votes && block < B)
+    for (int l = threadIdx.x; l < L; l += 256) votes[(size_t)block * L + l] = 0;
   // The solve counter the class kernel's flags are stamped with (see k_dp_class_fronts):
   // advanced here, on the device, so that a captured and replayed solve advances it as well.
   // epoch[1]: the counter has wrapped and the flags still have to be cleared, which the next
@@ -1328,7 +1330,8 @@ void launch_prepare(const Shape &s, const float *T, const int32_t *O, const floa
   hipLaunchKernelGGL(k_bin_unit, dim3((unsigned)s.B + nb_rc), dim3(256), 0, st, s.B, w.Oq,
                      w.budget, w.budget0, w.unit, w.minO, w.lowsum, w.topsum, w.status,
                      w.status_acc, s.L, s.SP, s.M, compress_bins ? 1 : 0, all_rows ? 1 : 0, w.Rt,
-                     w.cmeta, w.cstart, w.Rc, s.K, s.NC, w.epoch, w.bounds, s.S);
+                     w.cmeta, w.cstart, w.Rc, s.K, s.NC, w.epoch, w.bounds, w.votes,
+                     s.S);
 }
 
 void launch_layout_classes(const int32_t *desc, int S, int32_t *r_class, int32_t *count_out,

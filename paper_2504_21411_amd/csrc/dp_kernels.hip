@@ -513,13 +513,19 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
 // fl(C[i] + lo[i]) > U is, because the rounded add is monotone, strictly larger than the
 // minimum for every target: leaving it out changes neither the minimum nor the lowest index
 // that attains it.  A wave scans, in ascending order, the sources that some row of its 64
-// needs.  How many remain depends on the tables: layer times that differ by more than the
-// transition costs leave 10 to 18 of 44 and 15 to 20 of 96, and fewer the fewer targets share
-// a wave (cost model on 1024 devices: 60 of 242 with 16 targets, 100 with 32, 200 with all),
-// while costs that dwarf the differences leave all; then the wave takes the plain scan.
+// needs.  How many remain depends on the tables: with layer times of 1 to 10 and transition
+// costs of up to 1 / 2 / 4 about 5 / 8 / 16 of 44, 10 / 18 / 36 of 96, 18 / 37 / 73 of 242 with
+// 16 targets per bound; all of them where every source has a forbidden target.
+//
+// Whether the bounds pay is therefore found out as the solve goes along: in the first front
+// (and the fourth, or the sixteenth, and every power of four beyond) every tile bounds and
+// votes by how many sources stay, and an instance goes on bounding while the votes of its last
+// fronts (each front counting three quarters of the one after it: single fronts differ a lot)
+// are for it.  Elsewhere a tile goes straight to the plain scan.  Votes cost time, never
+// results.
 //
 // A workgroup owns a 64-row tile in LDS ([si][64], one row of +inf behind it); a wave owns JW
-// targets and keeps their running results in registers.
+// targets and keeps the running results of 8 G of them in registers.
 //   short scan  eight listed sources a step.  C[r][i] + R[i][j] is one V_MFMA_F32_4X4X1 per
 //     source and four targets: the accumulator input holds C of the lane's row four times,
 //     B = 1, and A holds the transition values, so each result is the same single rounded sum
@@ -530,12 +536,19 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
 //     four three-input minima (the running minimum among their operands) per chunk, the first
 //     chunk that attains the minimum is looked at again (see k_dp_tile).
 //
-// Bound by the vector ALU where little is left out, else by the latency of a tile's steps
-// (tile, bounds, list, gather; four waves per SIMD at 103 to 128 registers).  Whole searches,
-// before / after: 8 instances, 128 layers, 96 strategies, 16385 rows 5.11 / 3.86 ms; 4, 48, 242,
-// 4097 4.66 / 3.10 ms; 7, 17, 30, 778 155 / 137 us.  One bound over all targets is shared by the
-// workgroup's waves (each looks at the sources it fetched, 4 instructions a source); with more
-// than 128 strategies each wave bounds its own targets (6 a source, and their table columns).
+// Bound by the vector ALU where little is left out, else by the latency of a tile's steps.
+// Forms: eight targets a wave and as many waves as that takes (up to 16; 66 registers, 70
+// min-only), the shortest front on few tiles; two passes of eight for more tiles of 97 to 128
+// strategies (68 / 62) and, each wave bounding its own targets, beyond (80 / 76: one or two
+// workgroups per compute unit); sixteen at once there on few tiles (103: a workgroup per compute
+// unit holds no more anyway); 24 targets in each of four waves for many tiles of 73 to 96
+// strategies (128 / 84, 16 or 20 waves per compute unit), where the plain scan is k_dp_tile's,
+// since four waves per SIMD hide too little of one that reads the sources from LDS (1.05 against
+// 1.14 of the time of the kernel without bounds).  The compiler spills 20 to 75 scalar registers
+// of the backpointer forms and of the 24-target ones to vector lanes, none of the others.
+// One bound over all targets is shared by the workgroup's waves (each looks at the sources it
+// fetched, 4 instructions a source) and comes from a table; a wave that bounds its own targets
+// pays 6 a source and reads their table columns.
 // ---------------------------------------------------------------------------------------
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
@@ -548,6 +561,38 @@ static __device__ __forceinline__ float4_t mat_add(float a, const float4_t &cc) 
 static __device__ __forceinline__ float4_t mat_spread(float c) {
   const float4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
   return __builtin_amdgcn_mfma_f32_4x4x1f32(1.0f, c, z, 0, 0, 0);
+}
+
+// The lowest source of chunk g (eight of them) whose sum is m, one of the chunk's sums.
+static __device__ __forceinline__ int chunk_argmin(const float *tile_lane,
+                                                   const float *__restrict__ rc, float m, int g) {
+  const float *tg = tile_lane + 8 * g * kWave; // (differs from lane to lane, as does rg)
+  const float *__restrict__ rg = rc + 8 * g;
+  const float4 fa = *reinterpret_cast<const float4 *>(rg);
+  const float4 fb = *reinterpret_cast<const float4 *>(rg + 4);
+  const float rr[8] = {fa.x, fa.y, fa.z, fa.w, fb.x, fb.y, fb.z, fb.w};
+  int kk = 7;
+#pragma unroll
+  for (int k = 6; k >= 0; --k) kk = tg[k * kWave] + rr[k] == m ? k : kk;
+  return 8 * g + kk;
+}
+
+// Up to how many listed sources the short scan is the faster one, the bounds being paid for.
+// Measured with the scan forced one way and the other over transition costs of up to 1, 2, 3, 4,
+// 10 (see bound_pays): backpointers S = 30 about 18, 44 13 to 18, 64 13 to 23, 96 22 to 24, 128
+// 31 to 35, 200 48, 242 56; min-only 20, 28, 42, 64, 80, per wave S = 162 95, 242 140.
+template <int G, bool WITH_BP, bool GROUPED>
+static __device__ __forceinline__ int bound_brief(int S) {
+  if (WITH_BP) return GROUPED ? (S + 20) / 5 : G == 3 ? (3 * S + 20) / 10 : (S + 96) / 8;
+  return GROUPED ? (S + 16) / 2 : 5 * S / 8;
+}
+// ... and with how many bounds and short scan together take as long as a plain scan: S = 30 12,
+// 44 10 to 15, 64 11 to 19, 96 18 to 21 (30 with 24 targets a wave), 128 25 to 31, 200 31, 242 38;
+// min-only 15, 21, 35, 54, 65 to 80, per wave S = 162 55, 242 80.
+template <int G, bool WITH_BP, bool GROUPED>
+static __device__ __forceinline__ int bound_even(int S) {
+  if (WITH_BP) return G == 3 ? 3 * S / 10 : (S + 30) / 6;
+  return GROUPED ? (S + 24) / 3 : G == 3 ? 5 * S / 8 : 9 * S / 16;
 }
 
 // Four targets (half H of a group of eight) against eight listed sources id[].
@@ -572,30 +617,35 @@ static __device__ __forceinline__ void mat_step(float *m, int *g, float a, const
   }
 }
 
-template <int NW, int JW, bool WITH_BP, bool GROUPED>
-__global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(3))) void k_dp_bound(
+// G: groups of eight targets that a wave scans at once, NP: passes of those.
+template <int G, int NP, bool WITH_BP, bool GROUPED>
+__global__ __launch_bounds__(G < 3 ? 16 * kWave : 4 * kWave)
+__attribute__((amdgpu_waves_per_eu(G == 1 ? 6 : 4))) void k_dp_bound(
     const float *__restrict__ src, float *__restrict__ dst, uint8_t *__restrict__ bp,
     const float *__restrict__ Tq, const int32_t *__restrict__ Oq,
     const float *__restrict__ Rt, const float *__restrict__ bounds,
     const int32_t *__restrict__ ridx,
     const int32_t *__restrict__ budget, const int32_t *__restrict__ topsum,
-    const int32_t *__restrict__ lowsum, int B, int L, int S, int SP, int l, int pitch) {
-  // [8 np + 1][64], then [NW][8 np + 8] uint16 lists, and unless GROUPED [NW][64] partial
-  // bounds and [NW] masks
+    const int32_t *__restrict__ lowsum, int32_t *__restrict__ votes, bool probe, int B, int L,
+    int S, int SP, int l, int pitch) {
+  // [8 n8 + 1][64], then unless GROUPED [nw][64] partial bounds and [nw] masks, then
+  // [nw][8 n8 + 8] uint16 lists
   extern __shared__ float tile[];
-  constexpr int NU = (NW * JW + 63) / 64; // 64-source words
+  constexpr int JW = 8 * G * NP;       // targets (and fetched sources) of a wave
+  constexpr int NU = GROUPED ? 4 : 2;  // 64-source words
   const int b = blockIdx.x % B;
   const int js = wave_uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int tile_start = (int)(blockIdx.x / B) * kWave;
   const int E = budget[b];
   if (tile_start > E) return; // whole workgroup
-  const int np = (S + 15) / 16 * 2; // steps of eight sources, a whole number of pairs
-  float *part = tile + (8 * np + 1) * kWave; // (not there when GROUPED)
-  unsigned *masks = reinterpret_cast<unsigned *>(part + NW * kWave);
+  const int nw = (S + JW - 1) / JW; // waves of the workgroup
+  const int n8 = (S + 7) / 8;       // chunks of eight sources
+  float *part = tile + (8 * n8 + 1) * kWave; // (not there when GROUPED)
+  unsigned *masks = reinterpret_cast<unsigned *>(part + nw * kWave);
   uint16_t *list = (GROUPED ? reinterpret_cast<uint16_t *>(part)
-                            : reinterpret_cast<uint16_t *>(masks + NW)) +
-                   js * (8 * np + 8);
+                            : reinterpret_cast<uint16_t *>(masks + nw)) +
+                   js * (8 * n8 + 8);
 
   const int row = tile_start + lane;
   const bool valid = row <= E;
@@ -611,9 +661,27 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(3))) 
   const float *__restrict__ trow = Tq + (size_t)bl * SP;
   const int32_t *__restrict__ orow = Oq + (size_t)bl * SP;
   const int jbeg = js * JW;
-  const int jend = jbeg + JW < S ? jbeg + JW : S; // (<= jbeg: a wave without targets)
+  const int jend = jbeg + JW < S ? jbeg + JW : S;
 
+  // Have the bounds left enough out so far?  (No vote was cast in a front that did without.)
+  const int before = probe ? 0 : votes[bl - 1];
+  const bool bounded = probe || before > 0; // the same for all tiles of the instance
+  if (before > 0 && tile_start == 0 && threadIdx.x == 0) atomicAdd(votes + bl, before - before / 4);
   if (compute) {
+    // unless GROUPED: one bound for all targets, each wave looking at the sources it fetched;
+    // the table holds hi[SP], lo[SP] of this transition matrix
+    // (requested ahead of the tile where that takes few scalar registers)
+    float8_t hi8[JW / 8], lo8[JW / 8];
+    auto fetch_bounds = [&] {
+      // (a whole wave's share lies in the table's row, SP being a multiple of 16)
+      const float *t = bounds + (size_t)ridx[bl] * 2 * SP + jbeg;
+#pragma unroll
+      for (int x = 0; x < JW / 8; ++x) {
+        hi8[x] = *reinterpret_cast<const float8_t *>(t + 8 * x);
+        lo8[x] = *reinterpret_cast<const float8_t *>(t + SP + 8 * x);
+      }
+    };
+    if constexpr (!GROUPED && JW == 8) fetch_bounds();
     // sources JW js ...: JW loads of a wave in flight; padding is +inf
     const uint32_t rowc = (uint32_t)(valid ? row : E);
     float stage[JW];
@@ -626,141 +694,145 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(3))) 
     for (int u = 0; u < JW; ++u) {
       const int i = jbeg + u;
       stage[u] = (i < S && valid) ? stage[u] : GS_INF;
-      if (i < 8 * np) tile[i * kWave + lane] = stage[u];
+      if (i < 8 * n8) tile[i * kWave + lane] = stage[u];
     }
-    if (js == 0) tile[8 * np * kWave + lane] = GS_INF;
-    // rows whose result nobody reads need no source
-    const bool idle = row < low || row > top;
-    int n = 0; // listed sources
-    if constexpr (GROUPED) {
-      // lane i: bounds of sources i, i + 64, ... over this wave's targets
-      float hi[NU], lo[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        hi[u] = 0.0f;
-        lo[u] = GS_INF;
-        const int i = 64 * u + lane;
-        const float *col = rk + (i < SP ? i : SP - 1);
-#pragma unroll
-        for (int x = 0; x < JW; ++x) {
-          const int j = jbeg + x < S ? jbeg + x : S - 1; // (the last target again)
-          const float v = col[(size_t)j * SP];
-          hi[u] = __builtin_fmaxf(hi[u], v);
-          lo[u] = __builtin_fminf(lo[u], v);
-        }
-      }
+    int n = S; // listed sources
+    if (!bounded) {
       __syncthreads();
-      float bound = GS_INF;
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-        for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) { // (padding rows are +inf)
-          const float *tq = tile + (64 * u + i0) * kWave + lane;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const float h = __builtin_bit_cast(
-                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, hi[u]), i0 + k));
-            bound = __builtin_fminf(bound, tq[k * kWave] + h);
-          }
-        }
-      bound = idle ? -1.0f : bound;
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        unsigned long long word = 0;
-        for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) {
-          const float *tq = tile + (64 * u + i0) * kWave + lane;
-          unsigned bits = 0;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const float h = __builtin_bit_cast(
-                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lo[u]), i0 + k));
-            bits |= __builtin_amdgcn_ballot_w64(tq[k * kWave] + h <= bound) != 0 ? 1u << k : 0u;
-          }
-          word |= (unsigned long long)bits << i0;
-        }
-        if (64 * u + 64 > S) word &= 64 * u < S ? ~0ull >> (64 * u + 64 - S) : 0ull;
-        const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
-        if (word >> lane & 1) list[at] = (uint16_t)(64 * u + lane);
-        n += __builtin_popcountll(word);
-      }
     } else {
-      // one bound for all targets, each wave looking at the sources it fetched; the table
-      // holds hi[SP], lo[SP] of this transition matrix
-      const float *__restrict__ hi = bounds + (size_t)ridx[bl] * 2 * SP + jbeg;
-      const float *__restrict__ lo = hi + SP;
-      float bound = GS_INF;
+      n = 0;
+      if (js == 0) tile[8 * n8 * kWave + lane] = GS_INF;
+      // rows whose result nobody reads need no source
+      const bool idle = row < low || row > top;
+      if constexpr (GROUPED) {
+        // lane i: bounds of sources i, i + 64, ... over this wave's targets
+        float hi[NU], lo[NU];
 #pragma unroll
-      for (int u = 0; u < JW; ++u) bound = __builtin_fminf(bound, stage[u] + hi[u]);
-      if constexpr (NW > 1) {
+        for (int u = 0; u < NU; ++u) {
+          hi[u] = 0.0f;
+          lo[u] = GS_INF;
+          const int i = 64 * u + lane;
+          const float *col = rk + (i < SP ? i : SP - 1);
+#pragma unroll
+          for (int x = 0; x < JW; ++x) {
+            const int j = jbeg + x < S ? jbeg + x : S - 1; // (the last target again)
+            const float v = col[(size_t)j * SP];
+            hi[u] = __builtin_fmaxf(hi[u], v);
+            lo[u] = __builtin_fminf(lo[u], v);
+          }
+        }
+        __syncthreads();
+        float bound = GS_INF;
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) { // (padding rows are +inf)
+            const float *tq = tile + (64 * u + i0) * kWave + lane;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const float h = __builtin_bit_cast(
+                  float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, hi[u]), i0 + k));
+              bound = __builtin_fminf(bound, tq[k * kWave] + h);
+            }
+          }
+        bound = idle ? -1.0f : bound;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          unsigned long long word = 0;
+          for (int i0 = 0; i0 < 64 && 64 * u + i0 < S; i0 += 8) {
+            const float *tq = tile + (64 * u + i0) * kWave + lane;
+            unsigned bits = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const float h = __builtin_bit_cast(
+                  float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lo[u]), i0 + k));
+              bits |= __builtin_amdgcn_ballot_w64(tq[k * kWave] + h <= bound) != 0 ? 1u << k : 0u;
+            }
+            word |= (unsigned long long)bits << i0;
+          }
+          if (64 * u + 64 > S) word &= 64 * u < S ? ~0ull >> (64 * u + 64 - S) : 0ull;
+          const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
+          if (word >> lane & 1) list[at] = (uint16_t)(64 * u + lane);
+          n += __builtin_popcountll(word);
+        }
+      } else {
+        if constexpr (JW > 8) fetch_bounds();
+        float bound = GS_INF;
+#pragma unroll
+        for (int u = 0; u < JW; ++u) bound = __builtin_fminf(bound, stage[u] + hi8[u / 8][u % 8]);
         part[js * kWave + lane] = bound;
         __syncthreads();
+        for (int u = 0; u < nw; u += 4) { // (the last one again behind the end)
 #pragma unroll
-        for (int u = 0; u < NW; ++u) bound = __builtin_fminf(bound, part[u * kWave + lane]);
-      }
-      bound = idle ? -1.0f : bound;
-      unsigned bits = 0;
-#pragma unroll
-      for (int u = 0; u < JW; ++u)
-        bits |= __builtin_amdgcn_ballot_w64(stage[u] + lo[u] <= bound) != 0 ? 1u << u : 0u;
-      if (lane == 0) masks[js] = bits;
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int i = 64 * u + lane;
-        const bool on = i < S && (masks[i < NW * JW ? i / JW : 0] >> (i % JW) & 1u) != 0;
-        const unsigned long long word = __builtin_amdgcn_ballot_w64(on);
-        const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
-        if (on) list[at] = (uint16_t)i;
-        n += __builtin_popcountll(word);
-      }
-    }
-    const int steps = (n + 7) / 8;
-    if (n + lane < 8 * steps) list[n + lane] = (uint16_t)(8 * np); // the row of +inf
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (jbeg < S) {
-      auto store = [&](int j, float v, int from) {
-        const int eo = row + orow[j];
-        if (row >= low && eo <= E) {
-          (dstb + (size_t)j * pitch)[(uint32_t)eo] = v + trow[j];
-          if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)from;
+          for (int k = 0; k < 4; ++k)
+            bound = __builtin_fminf(bound, part[(u + k < nw ? u + k : nw - 1) * kWave + lane]);
         }
-      };
-      // A listed source costs about three times a source of the plain scan (compare and select
-      // for each, and the adds do not overlap the minima: 22 cycles for four sums and their
-      // minima where either alone takes 8), twice without the argmin; a plain scan pays 30
-      // instructions a target for the chunk's second look, or 90 sources' worth over ten.
-      const bool brief = WITH_BP ? 10 * n <= 3 * S + 90 : 2 * n <= S + 8; // wave-uniform
-      if (brief) {
-        float m[JW];
-        int g[JW];
+        bound = idle ? -1.0f : bound;
+        unsigned bits = 0;
 #pragma unroll
-        for (int x = 0; x < JW; ++x) {
+        for (int u = 0; u < JW; ++u)
+          bits |= __builtin_amdgcn_ballot_w64(stage[u] + lo8[u / 8][u % 8] <= bound) != 0 ? 1u << u : 0u;
+        if (lane == 0) masks[js] = bits;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          if (64 * u >= S) break;
+          const int i = 64 * u + lane;
+          const bool on = i < S && (masks[i < S ? i / JW : 0] >> (i % JW) & 1u) != 0;
+          const unsigned long long word = __builtin_amdgcn_ballot_w64(on);
+          const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(word >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((unsigned)word, 0));
+          if (on) list[at] = (uint16_t)i;
+          n += __builtin_popcountll(word);
+        }
+      }
+      if (n + lane < (n + 7) / 8 * 8) list[n + lane] = (uint16_t)(8 * n8); // the row of +inf
+      // (a third more is let pass where nothing is known yet: first fronts keep more sources)
+      if (js == 0 && lane == 0)
+        atomicAdd(votes + bl, bound_even<G, WITH_BP, GROUPED>(S) * (probe ? 4 : 3) / 3 - n);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    auto store = [&](int j, float v, int from) {
+      const int eo = row + orow[j];
+      if (row >= low && eo <= E) {
+        (dstb + (size_t)j * pitch)[(uint32_t)eo] = v + trow[j];
+        if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)from;
+      }
+    };
+    if (bounded && n <= bound_brief<G, WITH_BP, GROUPED>(S)) { // wave-uniform
+      const int steps = (n + 7) / 8;
+      const int k_own = (lane >> 2) & 7;
+#pragma unroll 1
+      for (int j0 = jbeg; j0 < jend; j0 += 8 * G) {
+        float m[8 * G];
+        int g[8 * G];
+#pragma unroll
+        for (int x = 0; x < 8 * G; ++x) {
           m[x] = GS_INF;
           g[x] = 0;
         }
-        // A operand of targets 8x .. 8x+7 against a step's eight sources: lane 4 (8 h + k) + i
-        // holds target 8x + 4h + i, source k of the step
-        const float *ra[JW / 8];
+        // A operand of targets 8x .. 8x+7 of the pass against a step's eight sources: lane
+        // 4 (8 h + k) + i holds target 8x + 4h + i, source k of the step
+        const float *ra[G];
 #pragma unroll
-        for (int x = 0; x < JW / 8; ++x) {
-          const int j = jbeg + 8 * x + 4 * (lane >> 5) + (lane & 3);
+        for (int x = 0; x < G; ++x) {
+          const int j = j0 + 8 * x + 4 * (lane >> 5) + (lane & 3);
           ra[x] = rk + (size_t)(j < SP ? j : SP - 1) * SP;
         }
-        const int k_own = (lane >> 2) & 7;
-        float a[JW / 8]; // (steps > 0: a row that is read needs a source)
+        float a[G]; // (steps > 0: a row that is read needs a source)
         {
           const int own = steps > 0 ? list[k_own] : 0;
 #pragma unroll
-          for (int x = 0; x < JW / 8; ++x) a[x] = ra[x][own < SP ? own : SP - 1];
+          for (int x = 0; x < G; ++x) a[x] = ra[x][own < SP ? own : SP - 1];
         }
+#pragma unroll 1
         for (int p = 0; p < steps; ++p) {
           // the next step's values are requested while these are used
           const int own = list[8 * (p + 1 < steps ? p + 1 : p) + k_own];
-          float an[JW / 8];
+          float an[G];
 #pragma unroll
-          for (int x = 0; x < JW / 8; ++x) an[x] = ra[x][own < SP ? own : SP - 1];
+          for (int x = 0; x < G; ++x) an[x] = ra[x][own < SP ? own : SP - 1];
           int id[8];
           float4_t cc[8];
 #pragma unroll
@@ -769,74 +841,69 @@ __global__ __launch_bounds__(NW *kWave) __attribute__((amdgpu_waves_per_eu(3))) 
             cc[k] = mat_spread(tile[id[k] * kWave + lane]);
           }
 #pragma unroll
-          for (int x = 0; x < JW / 8; ++x) {
+          for (int x = 0; x < G; ++x) {
             mat_step<0, WITH_BP>(m + 8 * x, g + 8 * x, a[x], cc, id);
             mat_step<1, WITH_BP>(m + 8 * x, g + 8 * x, a[x], cc, id);
             a[x] = an[x];
           }
         }
 #pragma unroll
-        for (int x = 0; x < JW; ++x)
-          if (jbeg + x < S) store(jbeg + x, m[x], g[x]);
-      } else {
-        // JB targets a pass as in k_dp_wide: 16 (8 for four targets) scalar transition values
-        // of each, the next ones requested while these are used (SP is a multiple of 16)
-        constexpr int JB = WITH_BP ? 2 : 4;
-        constexpr int W = WITH_BP ? 16 : 8;
-        typedef float vec_t __attribute__((ext_vector_type(W)));
-        const int nq = (S + W - 1) / W;
-        for (int j0 = jbeg; j0 < jend; j0 += JB) {
-          const float *__restrict__ rc[JB];
-          float mx[JB];
-          int gx[JB];
-          vec_t r[JB];
+        for (int x = 0; x < 8 * G; ++x)
+          if (j0 + x < S) store(j0 + x, m[x], g[x]);
+      }
+    } else if constexpr (G == 3 && WITH_BP) {
+      // (its registers hold a whole row of sources, and its four waves per SIMD hide too little
+      // of a scan that reads them from LDS: k_dp_tile's scan)
+      float c[96];
+#pragma unroll
+      for (int i = 0; i < 96; ++i) c[i] = i < 8 * n8 ? tile[i * kWave + lane] : GS_INF;
+      for (int j = jbeg; j < jend; ++j) {
+        const float *__restrict__ rc = rk + (size_t)j * SP;
+        float m = GS_INF;
+        int from = 0;
+        scan_chunks<96, true, 96>(m, from, c, rc);
+        store(j, m, chunk_argmin(tile + lane, rc, m, from));
+      }
+    } else {
+      // four targets a pass as in k_dp_wide, eight scalar transition values of each, the next
+      // ones requested while these are used
+      constexpr int JB = 4;
+      for (int j0 = jbeg; j0 < jend; j0 += JB) {
+        const float *__restrict__ rc[JB];
+        float mx[JB];
+        int gx[JB];
+        float8_t r[JB];
+#pragma unroll
+        for (int x = 0; x < JB; ++x) {
+          rc[x] = rk + (size_t)(j0 + x < jend ? j0 + x : j0) * SP;
+          mx[x] = GS_INF;
+          gx[x] = 0;
+          r[x] = *reinterpret_cast<const float8_t *>(rc[x]);
+        }
+        for (int q = 0; q < n8; ++q) {
+          const int qn = q + 1 < n8 ? q + 1 : q;
+          float8_t rn[JB];
+#pragma unroll
+          for (int x = 0; x < JB; ++x) rn[x] = *reinterpret_cast<const float8_t *>(rc[x] + 8 * qn);
+          const float *tq = tile + 8 * q * kWave + lane;
+          float c[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) c[k] = tq[k * kWave];
 #pragma unroll
           for (int x = 0; x < JB; ++x) {
-            rc[x] = rk + (size_t)(j0 + x < jend ? j0 + x : j0) * SP;
-            mx[x] = GS_INF;
-            gx[x] = 0;
-            r[x] = *reinterpret_cast<const vec_t *>(rc[x]);
-          }
-          for (int q = 0; q < nq; ++q) {
-            const int qn = q + 1 < nq ? q + 1 : q;
-            vec_t rn[JB];
+            float mn = mx[x];
 #pragma unroll
-            for (int x = 0; x < JB; ++x) rn[x] = *reinterpret_cast<const vec_t *>(rc[x] + W * qn);
-#pragma unroll
-            for (int h = 0; h < W / 8; ++h) {
-              const float *tq = tile + (W * q + 8 * h) * kWave + lane;
-              float c[8];
-#pragma unroll
-              for (int k = 0; k < 8; ++k) c[k] = tq[k * kWave];
-#pragma unroll
-              for (int x = 0; x < JB; ++x) {
-                float mn = mx[x];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) mn = __builtin_fminf(mn, c[k] + r[x][8 * h + k]);
-                if (WITH_BP) gx[x] = mn < mx[x] ? W / 8 * q + h : gx[x];
-                mx[x] = mn;
-              }
-            }
-#pragma unroll
-            for (int x = 0; x < JB; ++x) r[x] = rn[x];
+            for (int k = 0; k < 8; ++k) mn = __builtin_fminf(mn, c[k] + r[x][k]);
+            if (WITH_BP) gx[x] = mn < mx[x] ? q : gx[x];
+            mx[x] = mn;
           }
 #pragma unroll
-          for (int x = 0; x < JB; ++x) {
-            const int j = j0 + x;
-            if (j >= jend) break;
-            if (WITH_BP) {
-              const float *__restrict__ rg = rc[x] + 8 * gx[x];
-              const float *tg = tile + 8 * gx[x] * kWave + lane;
-              const float4 fa = *reinterpret_cast<const float4 *>(rg);
-              const float4 fb = *reinterpret_cast<const float4 *>(rg + 4);
-              const float rr[8] = {fa.x, fa.y, fa.z, fa.w, fb.x, fb.y, fb.z, fb.w};
-              int kk = 7; // (one of the chunk's sums is the minimum)
+          for (int x = 0; x < JB; ++x) r[x] = rn[x];
+        }
 #pragma unroll
-              for (int k = 6; k >= 0; --k) kk = tg[k * kWave] + rr[k] == mx[x] ? k : kk;
-              gx[x] = 8 * gx[x] + kk;
-            }
-            store(j, mx[x], gx[x]);
-          }
+        for (int x = 0; x < JB; ++x) {
+          if (j0 + x >= jend) break;
+          store(j0 + x, mx[x], WITH_BP ? chunk_argmin(tile + lane, rc[x], mx[x], gx[x]) : 0);
         }
       }
     }
@@ -2452,51 +2519,67 @@ static void launch_wide(const Shape &s, const Workspace &w, int l, const float *
   else launch_wide_as<uint8_t, true>(s, w, l, src, dst, bp_l, st);
 }
 
-template <int NW, int JW, bool GROUPED>
+template <int G, int NP, bool GROUPED>
 static void launch_bound_as(const Shape &s, const Workspace &w, int l, const float *src, float *dst,
                             void *bp_l, hipStream_t st) {
   const long long tiles = (s.M + 1 + kWave - 1) / kWave;
-  const dim3 grid((unsigned)(tiles * s.B)), block(NW * kWave);
-  const size_t n8 = (size_t)(s.S + 15) / 16 * 16;
-  const size_t lds = sizeof(float) * ((n8 + 1) * kWave + (GROUPED ? 0 : NW * kWave + NW)) +
-                     sizeof(uint16_t) * NW * (n8 + 8);
+  constexpr int JW = 8 * G * NP;
+  const int nw = (s.S + JW - 1) / JW;
+  const dim3 grid((unsigned)(tiles * s.B)), block(nw * kWave);
+  const size_t n8 = (size_t)(s.S + 7) / 8 * 8;
+  const size_t lds = sizeof(float) * ((n8 + 1) * kWave + (GROUPED ? 0 : nw * kWave + nw)) +
+                     sizeof(uint16_t) * nw * (n8 + 8);
   if (lds > 64 * 1024)
-    lds_opt_in(bp_l ? (const void *)k_dp_bound<NW, JW, true, GROUPED>
-                    : (const void *)k_dp_bound<NW, JW, false, GROUPED>,
+    lds_opt_in(bp_l ? (const void *)k_dp_bound<G, NP, true, GROUPED>
+                    : (const void *)k_dp_bound<G, NP, false, GROUPED>,
                lds, s.grants);
+  // fronts that bound in any case: the first, (4,) 16, 64, 256, ...
+  int p = JW > 8 ? 16 : 4;
+  while (p < l) p *= 4;
+  const bool probe = l == 1 || l == p;
   if (bp_l)
-    hipLaunchKernelGGL((k_dp_bound<NW, JW, true, GROUPED>), grid, block, lds, st, src, dst,
+    hipLaunchKernelGGL((k_dp_bound<G, NP, true, GROUPED>), grid, block, lds, st, src, dst,
                        (uint8_t *)bp_l, w.Tq, w.Oq, w.Rt, w.bounds, w.ridx, w.budget, w.topsum,
-                       w.lowsum, s.B, s.L, s.S, s.SP, l, s.pitch);
+                       w.lowsum, w.votes, probe, s.B, s.L, s.S, s.SP, l, s.pitch);
   else
-    hipLaunchKernelGGL((k_dp_bound<NW, JW, false, GROUPED>), grid, block, lds, st, src, dst,
+    hipLaunchKernelGGL((k_dp_bound<G, NP, false, GROUPED>), grid, block, lds, st, src, dst,
                        (uint8_t *)nullptr, w.Tq, w.Oq, w.Rt, w.bounds, w.ridx, w.budget, w.topsum,
-                       w.lowsum, s.B, s.L, s.S, s.SP, l, s.pitch);
+                       w.lowsum, w.votes, probe, s.B, s.L, s.S, s.SP, l, s.pitch);
 }
-// Which shapes take the bounded kernel by themselves, and in how many waves per tile.  Measured
-// against the kernels below over 12 layers, layer times of 1 to 10 and transition costs of up
-// to 1 / 2 / 4 (how far the bounds reach depends on that ratio; new / old time, the last of
-// the three with little left out):
-//   with backpointers  S = 44, 16 and 128 tiles 0.73 / 0.78 / 0.94 and 0.78 / 0.90 / 0.99, 520
-//     tiles 0.95 / 1.06 / 1.18 (not taken); S = 64, 520 tiles 0.75 / 0.87 / 1.00, 4 K tiles 1.17 at
-//     worst (not taken); S = 96, 4 K tiles 0.61 / 0.79 / 1.05, the 64-device cost model 0.76;
-//     S = 128, 520 tiles 0.59 / 0.77 / 1.05; S = 162 0.67 / 0.80 / 1.17 (not taken); S = 242,
-//     128 tiles 0.47 / 0.61 / 0.86, the 1024-device cost model 0.65, 2 K tiles 1.38 at worst
-//   without            S = 44, 128 tiles 0.82 / 0.84 / 0.96; S = 64, 4 K tiles 0.75 / 0.84 / 0.94;
-//     S = 96, 4 K tiles 0.61 / 0.65 / 0.80; S = 128 0.55 / 0.65 / 0.85; S = 162 0.63 / 0.70 / 0.80;
-//     S = 242, 128 tiles 0.45 / 0.51 / 0.63, 2 K tiles 0.71 / 0.81 / 1.00
-// Few targets per wave while the batch has few tiles (a front is one wave's length then), more
-// when the set-up of each wave counts.
+// Which shapes take the bounded kernel by themselves.  Measured against the kernels below, whole
+// solves of 12 layers, layer times of 1 to 10 and transition costs of up to 1 / 2 / 4 / 10 (how
+// far the bounds reach depends on that ratio; nothing is left out in the last one, which is also
+// what tables with a forbidden target per source take), new / old time:
+//   with backpointers  S = 30, 16 tiles 0.83 / 0.84 / 0.93 / 1.03, 256 tiles 0.86 / 0.92 / 1.02 /
+//     1.03 (S = 25: 1.10, not taken); S = 44, 256 tiles 0.81 / 0.87 / 0.93 / 0.93 (520 tiles of the
+//     encoder-decoder batch lose: not taken); S = 64, 128 tiles 0.84 / 1.01 / 1.03 / 1.04, 512 tiles
+//     0.79 / 0.92 / 0.94 / 0.93, 1024 tiles 0.92 / 1.11 / 1.10 / 1.10 (not taken); S = 80, 256 tiles
+//     0.79 / 0.92 / 0.95 / 0.95, 512 tiles 0.91 / 1.12 / 1.12 / 1.11 (not taken: ten waves of eight
+//     targets sit unevenly on four SIMDs); S = 96, 16 tiles 0.63 / 0.78 / 0.85 / 0.85, 1024 tiles
+//     0.75 / 0.94 / 0.99 / 1.00, 2056 tiles 0.64 / 0.83 / 1.04 / 1.05, 8 K tiles 0.67 / 0.88 / 1.10 /
+//     1.11; S = 104, 512 tiles 0.70 / 0.90 / 0.96 / 0.95, 1024 tiles 0.75 / 1.07 / 1.10 / 1.10 (not
+//     taken); S = 128, 1024 tiles 0.68 / 0.97 / 0.99 / 0.98; S = 242, 16 tiles 0.49 / 0.69 / 0.72 /
+//     0.72, 1024 tiles 0.64 / 0.87 / 0.89 / 0.89
+//   without  S = 30, 16 tiles 0.92 / 0.93 / 0.96 / 1.03; S = 64, 16 tiles 0.80 / 0.86 / 0.94 / 1.06,
+//     512 tiles 0.75 / 0.80 / 0.90 / 0.96, 1024 tiles 0.87 / 0.92 / 1.04 / 1.14 (not taken); S = 80,
+//     1024 tiles 0.80 / 0.87 / 1.00 / 1.16 (not taken), 8 K tiles 0.66 / 0.71 / 0.86 / 1.15; S = 96, 1024 tiles 0.69 / 0.77 / 0.92 / 1.09,
+//     4 K tiles 0.56 / 0.59 / 0.71 / 1.05, 8 K tiles 0.62 / 0.66 / 0.81 / 1.15; S = 128, 1024 tiles
+//     0.59 / 0.66 / 0.84 / 1.09; S = 150, 128 tiles 0.75 / 0.83 / 1.01 / 1.02, 512 tiles 0.85 / 0.94 /
+//     1.13 / 1.19 (not taken: ten waves on four SIMDs again); S = 162, 2 K tiles 0.74 / 0.84 / 1.04 /
+//     1.14 (0.67 in the 256-device cost model); S = 242, 16 tiles 0.48 / 0.55 / 0.69 / 0.80, 2 K tiles 0.60 / 0.69 /
+//     0.92 / 0.96
+// (A solve of more layers probes less often: one front in twelve here, two in 127.)
 static bool bound_pays(const Shape &s, bool with_bp) {
   const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
   switch (s.SP) {
-    case 32: case 48: return tiles <= 256;
-    case 64: return !with_bp || tiles <= 1024;
-    case 96: return true;
-    case 128: return !with_bp || tiles <= 1024;
-    default: break;
+    case 32: return s.S > 28 && tiles <= 256;
+    case 48: return tiles <= 256;
+    case 64: return tiles <= 512;
+    case 96: return s.S > 84 || tiles <= (with_bp ? 256 : 512) || (!with_bp && tiles >= 2048);
+    case 128: return !with_bp || tiles <= (s.S > 112 ? 1024 : 512);
+    case 192: return !with_bp && (tiles <= 256 || s.S <= 144 || s.S > 160);
+    default: return !with_bp || tiles <= 1024;
   }
-  return s.SP > 128 && (!with_bp || (s.SP > 192 && tiles <= 1024));
 }
 
 // Whether a solve of this shape without transition classes runs the bounded kernel.  The knob
@@ -2506,26 +2589,28 @@ bool bound_applies(const Shape &s, bool with_bp) {
   if (s.tune.kernel >= 1 && s.tune.kernel <= 4) return s.tune.kernel == 4;
   return bound_pays(s, with_bp);
 }
-// The forms with one bound for all targets read it from a table.
-bool bound_needs_table(const Shape &s) { return s.SP <= 128; }
+// Beyond 128 strategies a bound over all targets is loose: each wave bounds its own.
+bool bound_needs_table(const Shape &s) { return s.S <= 128; }
 
-#define GS_BOUND(NW, JW, GR) return launch_bound_as<NW, JW, GR>(s, w, l, src, dst, bp_l, st)
+// The form (figures as above): 24 targets a wave from two rounds of workgroups on (four per
+// compute unit, 2048 tiles; S = 96, 1088 tiles 0.92 / 1.14 / 1.15 / 1.16 against 0.74 / 0.95 / 0.98 /
+// 0.99 with eight, 2056 tiles 0.64 / 0.83 / 1.04 / 1.05 against 0.75 / 0.95 / 1.04 / 1.04); two passes
+// of eight for S = 128 from 513 tiles on (1024 tiles 0.68 / 0.97 / 0.99 / 0.98 against 0.71 / 0.92 /
+// 1.08 / 1.08, min-only 0.59 / 0.66 / 0.84 / 1.09 against 0.69 / 0.76 / 0.94 / 1.15); per wave, sixteen
+// targets at once up to a quarter more tiles than compute units (S = 242, 260 tiles 0.47 / 0.66 /
+// 0.66 / 0.66 against 0.51 / 0.68 / 0.67 / 0.67; 512 tiles 0.68 / 1.03 / 1.07 / 1.08 against 0.63 /
+// 0.86 / 0.88 / 0.89).
 static void launch_bound(const Shape &s, const Workspace &w, int l, const float *src, float *dst,
                          void *bp_l, hipStream_t st) {
   const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
-  switch (s.SP) {
-    case 32: GS_BOUND(4, 8, false);
-    case 48: GS_BOUND(6, 8, false);
-    case 64: if (tiles <= 1024) GS_BOUND(8, 8, false); GS_BOUND(4, 16, false);
-    case 96: if (tiles <= 1024) GS_BOUND(12, 8, false); GS_BOUND(4, 24, false);
-    case 128: if (tiles <= 256 && bp_l) GS_BOUND(16, 8, false); GS_BOUND(8, 16, false);
-    default: break;
+  if (!bound_needs_table(s)) {
+    if (s.S > 192 && tiles <= 320) return launch_bound_as<2, 1, true>(s, w, l, src, dst, bp_l, st);
+    return launch_bound_as<1, 2, true>(s, w, l, src, dst, bp_l, st);
   }
-  // (one bound per wave: with many strategies a bound over all targets is loose)
-  if (s.SP <= 192) { if (tiles <= 1024) GS_BOUND(12, 16, true); GS_BOUND(8, 24, true); }
-  GS_BOUND(16, 16, true);
+  if (s.SP == 96 && tiles >= 2048) return launch_bound_as<3, 1, false>(s, w, l, src, dst, bp_l, st);
+  if (s.SP == 128 && tiles > 512) return launch_bound_as<1, 2, false>(s, w, l, src, dst, bp_l, st);
+  launch_bound_as<1, 1, false>(s, w, l, src, dst, bp_l, st);
 }
-#undef GS_BOUND
 
 const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const float *src,
                             float *dst, void *bp_l, ForwardKernel which, hipStream_t st) {
@@ -2533,7 +2618,7 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
   const int blocks_per_instance = (s.M + 1 + kRowsPerBlock - 1) / kRowsPerBlock;
   const dim3 grid((unsigned)((size_t)blocks_per_instance * s.B));
   const int tsp = tuned_sp_for(s.S);
-  if (w.bounded) {
+  if (w.votes) { // (see bound_applies)
     launch_bound(s, w, l, src, dst, bp_l, st);
     return "k_dp_bound";
   }

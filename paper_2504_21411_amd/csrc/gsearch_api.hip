@@ -252,6 +252,7 @@ gs::Workspace group_view(const gs::Shape &s, const gs::Workspace &w, int b0) {
   g.unit = w.unit + b0;
   g.minO = w.minO + (size_t)b0 * s.L;
   g.lowsum = w.lowsum + (size_t)b0 * s.L;
+  if (w.votes) g.votes = w.votes + (size_t)b0 * s.L;
   g.topsum = w.topsum + (size_t)b0 * s.L;
   return g;
 }
@@ -348,11 +349,12 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
 
   // One launch for all fronts of a small instance; else, with nothing known about R, the
   // bounded kernel where it applies.  Its table (2 SP <= 256 floats per matrix) takes the room
-  // of the class table (32 x 32 floats or more).
+  // of the class table (32 x 32 floats or more), its votes that of maxfit.
   const bool small = which == gs::ForwardKernel::Auto && gs::small_path_applies(s, with_bp);
-  w.bounded = which == gs::ForwardKernel::Auto && s.L > 1 && !p->r_class && !small &&
-              gs::bound_applies(s, with_bp);
-  w.bounds = w.bounded && gs::bound_needs_table(s) ? w.Rc : nullptr;
+  const bool bounded = which == gs::ForwardKernel::Auto && s.L > 1 && !p->r_class && !small &&
+                       gs::bound_applies(s, with_bp);
+  w.votes = bounded ? w.maxfit : nullptr;
+  w.bounds = bounded && gs::bound_needs_table(s) ? w.Rc : nullptr;
 
   // Transition classes: checked whenever the caller states them, exploited by the class
   // kernel when no particular kernel is forced and the shape has a register-tiled size.

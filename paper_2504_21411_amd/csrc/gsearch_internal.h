@@ -97,7 +97,9 @@ struct Workspace {
                      //              first strategies, +inf for padding classes
   float *bounds;     // [K][2][SP]   without r_class, in Rc's place: largest and least
                      //              R[si][.] over the targets (null: not filled)
-  int bounded;       // 1: the layer fronts run on k_dp_bound
+  int32_t *votes;    // [B][L]       the layer fronts run on k_dp_bound (null: they do not): per
+                     //              front, whether the instance's tiles found the bounds worth
+                     //              their time, summed.  In maxfit's place, cleared by k_bin_unit
   // Several layer fronts per launch of the class kernel (see k_dp_class_fronts):
   int32_t *maxfit;   // [B][L]       largest O[b][l][s] that fits the budget at all (0: none)
   unsigned *stop;    // one word: a bounded wait gave up somewhere in this solve
@@ -155,7 +157,7 @@ enum class ForwardKernel { Auto, Generic, Push, Tile };
 const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const float *src,
                             float *dst, void *bp_l, ForwardKernel which, hipStream_t st);
 // Whether k_dp_bound runs a solve without transition classes and with no kernel forced by a
-// flag (Workspace::bounded is set then), and whether its form reads the table
+// flag (Workspace::votes is set then), and whether its form reads the table
 // Workspace::bounds (which is built for no other solve).
 bool bound_applies(const Shape &s, bool with_bp);
 bool bound_needs_table(const Shape &s);
