@@ -1511,3 +1511,131 @@ def test_bounds_that_leave_nothing_out_cost_little(gs, S, B, M, flags, old):
                 ctx.gsearch_set_knob("kernel", kernel)
                 us.append(_forward_us(ctx, runner, dw))
         assert us[0] <= 1.2 * us[1], (S, kind, us)
+
+
+def _some_bounds_help(w, seed):
+    """Instances for which the bounds leave most sources out, some, and none, side by side: the
+    layer times of two thirds of them shrink against the transition costs."""
+    scale = np.array([1.0, 0.25, 0.02], np.float32)[np.random.RandomState(seed).randint(0, 3, w.B)]
+    w.T = (w.T * scale[:, None, None]).astype(np.float32)
+    return w
+
+
+# the forms of the bounded kernel and the rule that picks them, by strategies and 64-row tiles:
+# (S, B, M, L, flags); two or three tiles an instance
+BOUND_FORMS = [
+    (30, 40, 140, 20, 0), (30, 40, 140, 20, 4), (48, 60, 140, 8, 0), (64, 150, 140, 8, 0),
+    (64, 150, 140, 8, 4),                                     # eight targets a wave
+    (80, 80, 140, 18, 0), (96, 300, 140, 6, 0), (96, 300, 140, 6, 4),
+    (128, 100, 140, 6, 0), (128, 100, 140, 6, 4),
+    (85, 700, 130, 5, 0), (96, 700, 130, 4, 0),               # 24 targets, from 2048 tiles on
+    (73, 700, 130, 5, 4), (96, 700, 130, 4, 4),
+    (100, 200, 140, 5, 4), (113, 200, 140, 5, 0), (128, 200, 140, 4, 0),   # two passes of eight
+    (128, 200, 140, 4, 4),
+    (193, 60, 140, 5, 0), (242, 60, 140, 4, 4),               # sixteen, bounds per wave
+    (200, 110, 140, 4, 0), (256, 110, 140, 4, 4),             # two passes, bounds per wave
+    (129, 90, 140, 5, 4), (162, 110, 140, 18, 4),
+]
+
+
+@pytest.mark.parametrize("S,B,M,L,flags", BOUND_FORMS)
+def test_bounded_kernel_forms_by_size(gs, oracle_mod, S, B, M, L, flags):
+    """Every form that the default choice can reach, at sizes on its side of the rule, with
+    instances that go on bounding and others that stop (and, with 18 layers, are probed again)."""
+    _, runner = gs
+    for case, r in enumerate((0.5, 2.0)):
+        w = random_tables(f"form{S}_{case}", B, L, S, M, K=2, seed=900 + S + case,
+                          budget=np.where(np.arange(B) % 5 == 0, M - 37, M).astype(np.int32))
+        w.R *= np.float32(r / 2.0)
+        w = _some_bounds_help(w, S + case)
+        with runner.make_context(w, flags=flags) as ctx:
+            ctx.gsearch_set_knob("small", 0)
+            got = runner.to_numpy(runner.run_step(ctx, runner.DeviceWorkload(w), backtrace="all"))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_bound"
+        assert_same(got, oracle_batch(oracle_mod, w), w, f"flags={flags} r={r}")
+
+
+@pytest.mark.parametrize("S", [30, 44, 64, 96, 128, 162, 242])
+@pytest.mark.parametrize("flags", [0x1, 0x5])
+def test_bounded_kernel_whole_planes(gs, oracle_mod, S, flags):
+    """Kept planes are exported whole: every row of C and bp is the oracle's, also the rows that
+    lead to no plan, which a solve without kept planes leaves undefined."""
+    _, runner = gs
+    w = random_tables(f"planes{S}", 3, 5, S, 333, K=2, seed=S,
+                      budget=np.array([333, 100, 257], np.int32))
+    w.R *= np.float32(0.5)
+    w.O[0, 2, 5] = 0
+    w.T[2] *= np.float32(0.02)
+    with runner.make_context(w, flags=flags) as ctx:
+        ctx.gsearch_set_knob("kernel", 4)
+        ctx.gsearch_set_knob("small", 0)
+        runner.run_step(ctx, runner.DeviceWorkload(w), backtrace=None)
+        assert ctx.gsearch_forward_kernel() == "k_dp_bound"
+        C, bp = ctx.gsearch_export_planes(want_bp=flags == 0x1)
+        C, bp = C.cpu().numpy(), bp.cpu().numpy() if bp is not None else None
+    for b in range(w.B):
+        E = int(w.budget[b])
+        ref = oracle_mod.solve(w.T[b], w.O[b], w.R, w.r_index[b], E, want_planes=True)
+        assert np.array_equal(bits(C[b, :, :E + 1, :]), bits(ref["C"])), b
+        if bp is not None:
+            assert np.array_equal(bp[b, :, :E + 1, :], ref["bp"].astype(np.int32)), b
+
+
+@pytest.mark.parametrize("S", [30, 64, 96, 128, 162, 242])
+@pytest.mark.parametrize("flags", [0, 0x4])
+def test_bounded_kernel_at_the_ends_of_the_range(gs, oracle_mod, S, flags):
+    """The short scan adds on the matrix cores: subnormal costs keep their last bit, sums beyond
+    the largest number become +inf, large and subnormal terms round as one addition does.
+    Transition costs are far below the layer times, so that nearly all sources are left out."""
+    _, runner = gs
+    tiny, g = np.float32(2.0 ** -149), np.random.RandomState(S)
+    for kind in ("subnormal", "least normal", "overflow", "mixed"):
+        w = random_tables(f"ends{S}_{kind}", 4, 6, S, 150, K=2, seed=S)
+        k = g.randint(0, 200, w.R.shape).astype(np.float32)
+        if kind == "subnormal":
+            w.T, w.R = (g.randint(0, 1 << 20, w.T.shape).astype(np.float32) * tiny), k * tiny
+        elif kind == "least normal":                 # sums that leave the subnormal range
+            w.T = (g.randint(0, 1 << 23, w.T.shape).astype(np.float32) * tiny)
+            w.R = (k * np.float32(97.0)) * tiny
+        elif kind == "overflow":                     # the last layers' sums pass 3.4e38
+            w.T, w.R = w.T * np.float32(1.1e37), k * np.float32(1e34)
+        else:
+            w.T, w.R = np.where(g.rand(*w.T.shape) < 0.5, w.T, w.T * np.float32(1e-39)), k * tiny
+        w.T, w.R = w.T.astype(np.float32), np.ascontiguousarray(w.R, np.float32)
+        w.R[:, np.arange(S), np.arange(S)] = 0.0
+        ref = oracle_batch(oracle_mod, w)
+        with runner.make_context(w, flags=flags) as ctx:
+            ctx.gsearch_set_knob("kernel", 4)
+            ctx.gsearch_set_knob("small", 0)
+            got = runner.to_numpy(runner.run_step(ctx, runner.DeviceWorkload(w), backtrace="all"))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_bound"
+        assert_same(got, ref, w, f"{kind} flags={flags}")
+
+
+@pytest.mark.parametrize("S", [44, 96, 200])
+def test_bounded_kernel_votes_start_afresh(gs, oracle_mod, S):
+    """A captured solve replayed on other transition costs, from bounds that help to bounds that
+    do not and back, in several groups of instances: the votes are this solve's own."""
+    _, runner = gs
+    import torch
+    w = random_tables(f"votes{S}", 6, 20, S, 300, K=2, seed=S)
+    cheap, dear = (w.R * np.float32(0.25)).astype(np.float32), (w.R * np.float32(30)).astype(np.float32)
+    dw = runner.DeviceWorkload(w)
+    st = torch.cuda.Stream()
+    with runner.make_context(w) as ctx, torch.cuda.stream(st):
+        ctx.gsearch_set_instance_groups(3)
+        runner.run_step(ctx, dw, backtrace="all")
+        st.synchronize()
+        assert ctx.gsearch_forward_kernel() == "k_dp_bound"
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            captured = runner.run_step(ctx, dw, backtrace="all")
+        for rep, R in enumerate((cheap, dear, cheap)):
+            w.R = R
+            dw.R.copy_(torch.from_numpy(R).to(dw.device))
+            graph.replay()
+            got = runner.to_numpy(captured)
+            got["data_status"] = ctx.gsearch_data_status()
+            assert_same(got, oracle_batch(oracle_mod, w), w, f"replay {rep}")
