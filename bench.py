@@ -35,19 +35,21 @@ LDS_PEAK_TBS = 256 * 128 * 2.4e9 / 1e12
 PROFILED = os.path.join(ROOT, "profiles", "traffic.json")
 
 
-def ops_per_relaxation(kernel: str, mode: str, S: int) -> float:
+def ops_per_relaxation(kernel: str, mode: str, S: int):
     """Vector-ALU instructions per relaxation that the kernel's algorithm needs.
 
     min only: one add and half of a three-input minimum.  Flat argmin (push and generic
     kernels): add, compare, two selects.  Two-level argmin (tile kernel): per chunk of
     eight candidates eight adds, four minimum instructions, one compare and two selects
     (15/8), plus the second look at one chunk per target state (8 adds, 8 compares,
-    8 selects = 24 per S relaxations).  k_dp_bound leaves sources out, depending on
-    the tables; it is priced as if it scanned them all.
+    8 selects = 24 per S relaxations).  None for k_dp_bound, which leaves sources out: how
+    many it scans depends on the tables and is not counted, so it has no ALU fraction.
     """
+    if kernel == "k_dp_bound":
+        return None
     if mode == "nobp":
         return 1.5
-    if kernel in ("k_dp_tile", "k_dp_wide", "k_dp_bound"):
+    if kernel in ("k_dp_tile", "k_dp_wide"):
         return 15.0 / 8.0 + 24.0 / S
     return 4.0
 
@@ -71,6 +73,12 @@ def load_profiled():
             return json.load(f)
     except (OSError, ValueError):
         return {}
+
+
+def profile_of(kernel, entry):
+    """The profile entry, or nothing if it was taken of another kernel than the one that ran."""
+    name = str((entry or {}).get("kernel", "")).replace("void ", "").replace("gs::", "")
+    return dict(entry) if name.split("<")[0] == kernel else {}
 
 
 def cpu_baseline(w, cfg_index, target_relax=3.0e10):
@@ -276,7 +284,7 @@ def main():
         launch_s = fwd_ms * 1e-3 / launches
         key = f"{cfg_index}/{mode}" + (f"/groups{groups_forced}" if groups_forced else "") \
             + ("/perfront" if kernel == "k_dp_class" and args.fronts == 0 else "")
-        prof = dict((profiled.get("entries") or {}).get(key) or {})
+        prof = profile_of(kernel, (profiled.get("entries") or {}).get(key))
         fronts_per_launch = 1.0
         if kernel == "k_dp_class_fronts" and prof.get("calls") and prof.get("solves"):
             # a launch of this kernel covers up to 64 layer fronts: the profile's per-dispatch
@@ -301,10 +309,13 @@ def main():
             extra = dict(classes=n_class, longest_class=max_len, ops_per_row=opr_row)
         else:
             opr = ops_per_relaxation(kernel, "nobp" if nobp else "bp", w.S)
-            ops = opr * relax * executed / launches / groups        # executed, per launch
-            per_launch = ops / launch_s / 1e12
-            alu_frac = per_launch * groups / ALU_PEAK_TLANEOPS
-            executed_nominal = executed
+            if opr is None:
+                ops = per_launch = alu_frac = executed_nominal = None
+            else:
+                ops = opr * relax * executed / launches / groups    # executed, per launch
+                per_launch = ops / launch_s / 1e12
+                alu_frac = per_launch * groups / ALU_PEAK_TLANEOPS
+                executed_nominal = executed
             extra = dict(ops_per_relaxation=opr)
         hbm_gbs = front_bytes / launch_s / 1e9                  # same launches, bytes moved
         hbm_frac = hbm_gbs / HBM_PEAK_GBS
@@ -315,7 +326,8 @@ def main():
             lds_tbs = prof["lds_bytes"] * groups / launch_s / 1e12
             lds = {"achieved": lds_tbs, "peak": LDS_PEAK_TBS, "unit": "TB/s",
                    "frac": lds_tbs / LDS_PEAK_TBS, "bytes_per_launch_profiled": prof["lds_bytes"]}
-        if hbm_frac > alu_frac:
+        if alu_frac is None or hbm_frac > alu_frac:
+            # (no ALU fraction: the share of the HBM peak is stated, whatever bounds it)
             # few strategies per state (min-only pass of the outer-search batch): the plane
             # traffic, not the arithmetic, is the tighter roof
             roof = dict(common, bound="hbm", achieved=hbm_gbs, peak=HBM_PEAK_GBS, unit="GB/s",
@@ -345,7 +357,8 @@ def main():
         res = {"mode": mode, "ms_per_step": ms_step, "forward_ms": fwd_ms,
                "grelax_per_s": relax / (ms_step * 1e-3) / 1e9,
                "forward_grelax_per_s": relax / (fwd_ms * 1e-3) / 1e9,
-               "executed_grelax_per_s": relax * executed_nominal / (ms_step * 1e-3) / 1e9,
+               "executed_grelax_per_s": None if executed_nominal is None else
+               relax * executed_nominal / (ms_step * 1e-3) / 1e9,
                "kernel_avg_us": fwd_ms * 1e3 / launches,
                "roofline": roof, "best_instance": best, **extras}
         if groups > 1 and single_chain and not args.no_single_chain:

@@ -18,6 +18,34 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     assert not p.stdout.strip().startswith("{")
 
 
+def test_no_alu_fraction_without_a_count_and_no_counters_of_another_kernel():
+    """k_dp_bound's scans are not counted, so it is not priced as if it scanned every source; a
+    profile entry counts only for the kernel it was taken of."""
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.ops_per_relaxation("k_dp_bound", "bp", 96) is None
+    assert bench.ops_per_relaxation("k_dp_bound", "nobp", 96) is None
+    assert bench.ops_per_relaxation("k_dp_wide", "bp", 96) == 15 / 8 + 24 / 96
+    entry = {"kernel": "void k_dp_wide<unsigned char, 8, true, 2, 64>", "lds_bytes": 1.0}
+    assert bench.profile_of("k_dp_wide", entry) == entry
+    assert bench.profile_of("k_dp_bound", entry) == {} and bench.profile_of("k_dp_bound", None) == {}
+
+
+@pytest.mark.gpu
+def test_bench_reports_no_alu_fraction_for_the_bounded_kernel():
+    p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--mode", "bp-general",
+                        "--also=", "--also-configs=", "--no-cpu-baseline", "--steps", "2",
+                        "--warmup", "1", "--min-warmup-seconds", "0"],
+                       capture_output=True, text=True, timeout=600)
+    assert p.returncode == 0, p.stderr[-2000:]
+    d = json.loads(p.stdout)
+    r = d["roofline"]
+    assert r["kernel"] == "k_dp_bound" and r["alu_frac"] is None and r["bound"] == "hbm"
+    assert r["ops_per_relaxation"] is None and d["executed_grelax_per_s"] is None
+    assert 0 < r["frac"] <= 1.0 and 0 < r["frac_single_chain"] <= 1.0 and d["value"] > 0
+    assert r["traffic_profiled_kernel"] is None or "k_dp_bound" in r["traffic_profiled_kernel"]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("config", [0, 1])
 def test_bench_prints_one_json_line_with_the_contract_keys(config):
