@@ -2622,6 +2622,7 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
     launch_bound(s, w, l, src, dst, bp_l, st);
     return "k_dp_bound";
   }
+  // What the bounded kernel leaves (see bound_pays), and forced kernels.
   // Which register-tiled kernel: measured on MI355X, the LDS-staged two-level kernel wins
   // from 48 padded strategies up when backpointers are wanted (its argmin costs about 2.3
   // instead of 4 vector instructions per relaxation) and for 48..64 without them; the
@@ -2634,22 +2635,16 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
   // backpointers, 4 K without).
   const long long tile_inst = (long long)((s.M + kWave) / kWave) * s.Bc;
   if (tsp != 0 && tsp <= 32) use_tile = tile_inst <= (bp_l ? 16384 : 4096);
-  // Large S on a handful of tiles: the push kernel slices the strategies over up to eight
-  // workgroups per tile and fills more of the chip (S = 96, 64 tiles: 0.22 against 0.31 ms
-  // for 11 fronts).
-  if (tsp >= 64 && tile_inst <= 256) use_tile = false;
   // The LDS-streamed kernel (made for more than 128 strategies) also wins below that where
-  // the register-tiled ones run out of registers or of parallel work (measured, 7 fronts,
-  // ms: S = 128, 8 x 16385 rows: 0.79 against 0.85 with backpointers, 0.62 against 0.71
-  // without; S = 96 up to a few thousand tiles: configs[3] 6.9 against 7.3 ms with
-  // backpointers, 5.5 against 5.8 without, but 8 K tiles 2.04 against 1.87 and 1.46 against
-  // 1.27; S = 64 on a handful of tiles 0.08 against 0.09).
+  // the register-tiled ones run out of registers (measured, 7 fronts, ms: S = 128, 8 x 16385
+  // rows: 0.79 against 0.85 with backpointers, 0.62 against 0.71 without; 96 padded strategies up
+  // to a few thousand tiles, of which 65 to 84 strategies come here: S = 96, 2056 tiles, 127
+  // fronts 6.9 against 7.3 ms with backpointers, 5.5 against 5.8 without, but 8 K tiles 2.04
+  // against 1.87 and 1.46 against 1.27).
   // The knob "kernel" = 3 forces it wherever its tile fits.
   if (which == ForwardKernel::Auto && tsp == s.SP && s.SP % 16 == 0 && s.tune.kernel != 1 &&
       s.tune.kernel != 2) {
-    const bool wide = s.tune.kernel == 3 || tsp == 128 ||
-                      (tsp == 96 && tile_inst <= 4096) ||
-                      (tsp == 64 && tile_inst <= 256);
+    const bool wide = s.tune.kernel == 3 || tsp == 128 || (tsp == 96 && tile_inst <= 4096);
     if (wide) {
       launch_wide(s, w, l, src, dst, bp_l, st);
       return "k_dp_wide";

@@ -1639,3 +1639,19 @@ def test_bounded_kernel_votes_start_afresh(gs, oracle_mod, S):
             got = runner.to_numpy(captured)
             got["data_status"] = ctx.gsearch_data_status()
             assert_same(got, oracle_batch(oracle_mod, w), w, f"replay {rep}")
+
+
+@pytest.mark.parametrize("kernel,name", [(1, "k_dp_push"), (2, "k_dp_tile"), (3, "k_dp_wide")])
+@pytest.mark.parametrize("S", [49, 64, 80, 96, 100, 128])
+@pytest.mark.parametrize("flags", [0, 0x4])
+def test_general_kernels_forced_by_the_knob(gs, oracle_mod, S, kernel, name, flags):
+    """Shapes that run the bounded kernel by themselves, on each of the kernels without bounds."""
+    _, runner = gs
+    w = random_tables(f"forced{S}", 3, 5, S, 200, K=2, seed=S, budget=np.array([200, 77, 150], np.int32))
+    with runner.make_context(w, flags=flags) as ctx:
+        ctx.gsearch_set_knob("kernel", kernel)
+        ctx.gsearch_set_knob("small", 0)
+        got = runner.to_numpy(runner.run_step(ctx, runner.DeviceWorkload(w), backtrace="all"))
+        got["data_status"] = ctx.gsearch_data_status()
+        assert ctx.gsearch_forward_kernel() == name
+    assert_same(got, oracle_batch(oracle_mod, w), w, f"kernel={kernel} flags={flags}")
