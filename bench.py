@@ -296,7 +296,8 @@ def main():
         common = {"kernel": kernel, "concurrent_launches": groups,
                   "layer_fronts_per_launch": fronts_per_launch,
                   "traffic": prof.get("traffic_bytes"),
-                  "traffic_profiled_kernel": prof.get("kernel")}
+                  "traffic_profiled_kernel": prof.get("kernel"),
+                  "traffic_commit": prof.get("commit", profiled.get("commit")) if prof else None}
         if kernel.startswith("k_dp_class"):
             # With the transition classes the arithmetic shrinks to one minimum per class
             # and one relaxation per pair of classes, and with the compact planes the

@@ -96,11 +96,12 @@ LDS = "SQ_INSTS_LDS_LOAD SQ_INSTS_LDS_STORE SQ_INSTS_LDS_ATOMIC SQ_INSTS_LDS_LOA
 
 def write_markdown(d, folder, notes):
     """One short summary per kernel and workload, written from the same document as
-    traffic.json; older *.md files in the folder are removed."""
+    traffic.json; older *_cfg*.md files in the folder are removed.  An entry measured later than
+    the rest of the document brings its own "commit" and "written"."""
     commit = d["commit"]
     cal = d["calibration"]
     for old in os.listdir(folder):
-        if old.endswith(".md"):
+        if old.endswith(".md") and "_cfg" in old:
             os.remove(os.path.join(folder, old))
     groups = {}
     for key, e in d["entries"].items():
@@ -111,7 +112,9 @@ def write_markdown(d, folder, notes):
         path = os.path.join(folder, f"{kern}_{NAMES[cfg]}.md")
         out = []
         out.append(f"# {kern} on configs[{cfg}] ({SHAPES[cfg]}) — rocprofv3 summary, MI355X\n")
-        out.append(f"Measured at commit `{commit}` ({d['written']}); figures per dispatch of the forward kernel, "
+        commit_of = items[0][1].get("commit", commit)
+        written = items[0][1].get("written", d["written"])
+        out.append(f"Measured at commit `{commit_of}` ({written}); figures per dispatch of the forward kernel, "
                    f"averaged over the run. Written from `profiles/traffic.json` "
                    f"(`python -m paper_2504_21411_amd.profile_summary`).\n")
         out.append("Commands (from /tmp with TMPDIR=/tmp; `bench.py` is the repository's; `<B>` below):\n")
