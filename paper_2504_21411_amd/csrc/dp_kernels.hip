@@ -617,7 +617,9 @@ static __device__ __forceinline__ void mat_step(float *m, int *g, float a, const
   }
 }
 
-// G: groups of eight targets that a wave scans at once, NP: passes of those.
+// G: groups of eight targets that a wave scans at once, NP: passes of those.  Six waves per SIMD
+// are asked for with one group (80 registers at most; eight, or 64 registers, spill to memory and
+// take 1.2 of the time), four with more.
 template <int G, int NP, bool WITH_BP, bool GROUPED>
 __global__ __launch_bounds__(G < 3 ? 16 * kWave : 4 * kWave)
 __attribute__((amdgpu_waves_per_eu(G == 1 ? 6 : 4))) void k_dp_bound(
