@@ -268,10 +268,11 @@ __global__ void k_set_word(uint32_t *__restrict__ p, uint32_t v) {
 }
 
 // Layer fronts per launch of the class kernel (0: one launch per front).  The several-fronts
-// form needs the eight XCDs to take workgroups in turn and a batch that is a multiple of 8.
-int fronts_per_launch(const gsearch_ctx *ctx, const gs::Shape &s) {
+// form needs the eight XCDs to take workgroups in turn; a knob of 2 or more asks for it wherever
+// it can run.
+int fronts_per_launch(const gsearch_ctx *ctx, const gs::Shape &s, bool with_bp) {
   if (!ctx->fronts_ok || !gs::fronts_shape_ok(s) || ctx->groups > 1) return 0;
-  if (ctx->tune.fronts < 0) return 64;
+  if (ctx->tune.fronts < 0) return gs::fronts_pay(s, with_bp) ? 64 : 0;
   return ctx->tune.fronts >= 2 ? ctx->tune.fronts : 0;
 }
 
@@ -383,7 +384,7 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
     gs::launch_dp_small(s, w, keep, cur, st);
     ctx->forward_kernel = "k_dp_small";
     ctx->groups_used = 1;
-  } else if (use_classes && fronts_per_launch(ctx, s) > 0) {
+  } else if (use_classes && fronts_per_launch(ctx, s, with_bp) > 0) {
     // several layer fronts per launch, the instances bound to XCDs (see k_dp_class_fronts)
     if (keep) gs::launch_class_zero(s, w.planes, st);
     if (timing && hipEventRecord(ctx->ev_begin, st) != hipSuccess) return GSEARCH_ERR_HIP;
@@ -399,7 +400,7 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
         y0 = (int)seen + ((int)seen / 16 > 4 ? (int)seen / 16 : 4);
     }
     ctx->forward_kernel = gs::launch_dp_class_fronts(s, w, keep, with_bp, pe, bp_layer_bytes,
-                                                     fronts_per_launch(ctx, s), ring, y0,
+                                                     fronts_per_launch(ctx, s, with_bp), ring, y0,
                                                      ctx->front_hint, ctx->resident_wgs, st);
     ctx->groups_used = 1;
     cur = keep ? s.L - 1 : ((s.L - 1) & (ring - 1));

@@ -702,6 +702,52 @@ def test_class_kernel_several_fronts_per_launch(gs, oracle_mod, shape, mode):
         assert_same(got, ref, w, f"per front after several per launch {mode}")
 
 
+@pytest.mark.parametrize("jsplit", [0, 4, 8])
+@pytest.mark.parametrize("mode", ["bp", "nobp"])
+@pytest.mark.parametrize("shape", [(1, 9, 16, 63), (2, 17, 24, 700), (7, 8, 44, 640), (9, 10, 96, 500),
+                                   (13, 12, 44, 1000), (63, 8, 16, 130)],
+                         ids=lambda t: "B%dL%dS%dM%d" % t)
+def test_several_fronts_per_launch_for_any_batch(gs, oracle_mod, shape, mode, jsplit):
+    """Batches that leave XCDs without an instance or one instance short take the several-fronts
+    form by themselves (from eight layers up), with either number of waves per tile; budgets at the
+    edges of tiles, one that fits nothing."""
+    binding, runner = gs
+    import torch
+    B, L, S, M = shape
+    budget = np.array([(M, M // 64 * 64 - 1, M // 64 * 64, 2 * M // 3, M - 1)[b % 5] for b in range(B)],
+                      np.int32)
+    if B > 2:
+        budget[2] = 1
+    w, r_class = workloads.class_tables("anybatch", B, L, S, M, [4] * (S // 4), K=2, seed=B + S,
+                                        budget=budget, coarse=True)
+    ref = oracle_batch(oracle_mod, w)
+    dw = runner.DeviceWorkload(w)
+    rc = torch.from_numpy(r_class).to(dw.device)
+    with runner.make_context(w, flags=MODES[mode]) as ctx:
+        ctx.gsearch_set_knob("jsplit", jsplit)
+        for rep in range(3):                        # (the grid of later solves is sized by the first)
+            got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all", r_class=rc))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_class_fronts"
+            assert_same(got, ref, w, f"{mode} jsplit={jsplit} rep {rep}")
+
+
+def test_the_form_of_the_class_kernel_follows_the_load_of_an_xcd(gs):
+    """Which searches take several fronts per launch by themselves: not those whose uneven spread
+    over the XCDs, or whose long fronts, cost more than the launches saved."""
+    _, runner = gs
+    import torch
+    for B, L, S, M, flags, kernel in ((8, 3, 24, 200, 0, "k_dp_class_fronts"),
+                                      (9, 7, 24, 200, 0, "k_dp_class"), (9, 8, 24, 200, 0, "k_dp_class_fronts"),
+                                      (1, 8, 128, 8000, 0, "k_dp_class"), (8, 8, 128, 8000, 0, "k_dp_class_fronts"),
+                                      (8, 8, 24, 5000, 0, "k_dp_class_fronts"), (8, 8, 24, 5000, 4, "k_dp_class")):
+        w, r_class = workloads.class_tables("form", B, L, S, M, [4] * (S // 4), K=1, seed=B)
+        dw = runner.DeviceWorkload(w)
+        with runner.make_context(w, flags=flags) as ctx:
+            runner.run_step(ctx, dw, backtrace=None, r_class=torch.from_numpy(r_class).to(dw.device))
+            assert ctx.gsearch_forward_kernel() == kernel, (B, L, S, M, flags)
+
+
 def test_several_fronts_per_launch_on_other_streams_and_in_a_graph(gs, oracle_mod):
     """Which XCD the first workgroup of a launch lands on depends on the stream's hardware
     queue; the several-fronts form only needs an instance's workgroups to share an XCD.  Solves
