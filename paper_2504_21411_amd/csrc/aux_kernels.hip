@@ -13,8 +13,7 @@ namespace gs {
 //   wave < B*L            : one (b,l) row of T and O (lanes = strategies), r_index[b][l],
 //                           min_s O by a wave reduction
 //   remaining waves       : 64 consecutive entries each of the transposed transition pool
-//                           (incl. the padding row behind it, which the push kernel's
-//                           prefetch reads but never uses), then the budgets
+//                           (incl. a padding row behind it), then the budgets
 // ----------------------------------------------------------------------------------------
 static __device__ void prepare_part(
     int block, const float *__restrict__ T, const int32_t *__restrict__ O,

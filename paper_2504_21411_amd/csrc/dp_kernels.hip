@@ -11,13 +11,16 @@
 // wave scans si with the transition column R[.][sj] as wave-uniform scalar operands, then
 // adds T and stores to row e' + O[l][sj].  Every C operand is read from HBM/L2 once and
 // reused S times from registers, so the kernel is bound by the vector ALU (one add and
-// the min/argmin bookkeeping per relaxation), not by LDS or HBM.  The shifted stores
-// stay coalesced because O[l][sj] is uniform across the wave.
+// the min/argmin bookkeeping per relaxation), or, with few strategies on large batches, by the
+// planes' way through HBM (outer search, 24 strategies, 2048 instances: 175 us per front with
+// backpointers, 3.9 TB/s; 209 us with a flat argmin of four instructions per relaxation).  The
+// shifted stores stay coalesced because O[l][sj] is uniform across the wave.
 //
 // Rows e < O[l][sj] of the target cannot hold layer l under sj: they are set to +inf
 // (bp 0) by the wave that owns those rows, so that every row 0..E of the target plane is
 // written exactly once per launch and nothing stale survives from an earlier solve.
 #include "gsearch_internal.h"
+#include "pair_min.h"
 
 #include <type_traits>
 
@@ -29,170 +32,7 @@ static __device__ __forceinline__ int wave_uniform(int v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// ---------------------------------------------------------------------------------------
-// Argmin scan of the register-tiled kernel, written as inline assembly.
-//
-// Per relaxation the vector ALU executes exactly four instructions,
-//     v = c + r;   keep = (v >= m);   m = keep ? m : v;   arg = keep ? arg : idx
-// ("v >= m keeps" is the strict-less-than update of the recurrence; NaN cannot occur
-// because inputs are validated non-negative and +inf only ever meets +inf).
-// Left to the compiler, the index selects get deferred and all S compare masks are parked
-// in scalar registers and spilled, so the schedule is fixed by hand here:
-//   * two independent chains (even candidates -> chain A, odd -> chain B) are interleaved
-//     so that, between a compare that writes a lane mask into scalar registers and the
-//     selects that read it, two other vector instructions always issue (gfx950 requires
-//     two wait states there; the last step of a block has no adds left and uses s_nop);
-//   * chain-local indices n (candidate 2n or 2n+1) stay below 64, so they are inline
-//     constants and never compete with the mask for the constant bus;
-//   * the eight transition values of the NEXT block are fetched by one scalar load issued
-//     at the top of the block and awaited at its end, after 32 vector instructions.
-// One block handles candidates 8q .. 8q+7; `r` holds their transition costs, `rn`
-// receives those of the following eight (the first eight of the next column after the
-// last block: the caller keeps one padding row behind the table for that).
-// ---------------------------------------------------------------------------------------
 typedef float float8_t __attribute__((ext_vector_type(8)));
-
-template <int Q>
-static __device__ __forceinline__ void argmin_block8(float &mA, int &argA, float &mB, int &argB,
-                                                     const float *c, const float8_t &r,
-                                                     float8_t &rn, const float *col) {
-  float tA0, tB0, tA1, tB1;
-  unsigned long long maskA;
-  asm volatile(
-      "s_load_dwordx8 %[rn], %[col], %[n0]*8+32\n\t"
-      "v_add_f32 %[tA0], %[r0], %[c0]\n\t"
-      "v_add_f32 %[tB0], %[r1], %[c1]\n\t"
-      // step 0
-      "v_cmp_ge_f32 %[mk], %[tA0], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB0], %[mB]\n\t"
-      "v_add_f32 %[tA1], %[r2], %[c2]\n\t"
-      "v_add_f32 %[tB1], %[r3], %[c3]\n\t"
-      "v_cndmask_b32 %[mA], %[tA0], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0], %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB0], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0], %[aB], vcc\n\t"
-      // step 1
-      "v_cmp_ge_f32 %[mk], %[tA1], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB1], %[mB]\n\t"
-      "v_add_f32 %[tA0], %[r4], %[c4]\n\t"
-      "v_add_f32 %[tB0], %[r5], %[c5]\n\t"
-      "v_cndmask_b32 %[mA], %[tA1], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+1, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB1], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+1, %[aB], vcc\n\t"
-      // step 2
-      "v_cmp_ge_f32 %[mk], %[tA0], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB0], %[mB]\n\t"
-      "v_add_f32 %[tA1], %[r6], %[c6]\n\t"
-      "v_add_f32 %[tB1], %[r7], %[c7]\n\t"
-      "v_cndmask_b32 %[mA], %[tA0], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+2, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB0], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+2, %[aB], vcc\n\t"
-      // step 3
-      "v_cmp_ge_f32 %[mk], %[tA1], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB1], %[mB]\n\t"
-      "s_nop 0\n\t"
-      "v_cndmask_b32 %[mA], %[tA1], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+3, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB1], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+3, %[aB], vcc\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : [mA] "+v"(mA), [aA] "+v"(argA), [mB] "+v"(mB), [aB] "+v"(argB), [tA0] "=&v"(tA0),
-        [tB0] "=&v"(tB0), [tA1] "=&v"(tA1), [tB1] "=&v"(tB1), [mk] "=&s"(maskA),
-        [rn] "=&s"(rn)
-      : [col] "s"(col), [n0] "n"(4 * Q), [r0] "s"(r[0]), [r1] "s"(r[1]), [r2] "s"(r[2]),
-        [r3] "s"(r[3]), [r4] "s"(r[4]), [r5] "s"(r[5]), [r6] "s"(r[6]), [r7] "s"(r[7]),
-        [c0] "v"(c[8 * Q + 0]), [c1] "v"(c[8 * Q + 1]), [c2] "v"(c[8 * Q + 2]),
-        [c3] "v"(c[8 * Q + 3]), [c4] "v"(c[8 * Q + 4]), [c5] "v"(c[8 * Q + 5]),
-        [c6] "v"(c[8 * Q + 6]), [c7] "v"(c[8 * Q + 7])
-      : "vcc", "memory");
-}
-
-// Same eight-candidate block without the scalar prefetch: used for all but the last of the
-// RU row groups that share one set of transition values.
-template <int Q>
-static __device__ __forceinline__ void argmin_block8_shared(float &mA, int &argA, float &mB,
-                                                            int &argB, const float *c,
-                                                            const float8_t &r) {
-  float tA0, tB0, tA1, tB1;
-  unsigned long long maskA;
-  asm volatile(
-      "v_add_f32 %[tA0], %[r0], %[c0]\n\t"
-      "v_add_f32 %[tB0], %[r1], %[c1]\n\t"
-      "v_cmp_ge_f32 %[mk], %[tA0], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB0], %[mB]\n\t"
-      "v_add_f32 %[tA1], %[r2], %[c2]\n\t"
-      "v_add_f32 %[tB1], %[r3], %[c3]\n\t"
-      "v_cndmask_b32 %[mA], %[tA0], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0], %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB0], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0], %[aB], vcc\n\t"
-      "v_cmp_ge_f32 %[mk], %[tA1], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB1], %[mB]\n\t"
-      "v_add_f32 %[tA0], %[r4], %[c4]\n\t"
-      "v_add_f32 %[tB0], %[r5], %[c5]\n\t"
-      "v_cndmask_b32 %[mA], %[tA1], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+1, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB1], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+1, %[aB], vcc\n\t"
-      "v_cmp_ge_f32 %[mk], %[tA0], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB0], %[mB]\n\t"
-      "v_add_f32 %[tA1], %[r6], %[c6]\n\t"
-      "v_add_f32 %[tB1], %[r7], %[c7]\n\t"
-      "v_cndmask_b32 %[mA], %[tA0], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+2, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB0], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+2, %[aB], vcc\n\t"
-      "v_cmp_ge_f32 %[mk], %[tA1], %[mA]\n\t"
-      "v_cmp_ge_f32 vcc, %[tB1], %[mB]\n\t"
-      "s_nop 0\n\t"
-      "v_cndmask_b32 %[mA], %[tA1], %[mA], %[mk]\n\t"
-      "v_cndmask_b32 %[aA], %[n0]+3, %[aA], %[mk]\n\t"
-      "v_cndmask_b32 %[mB], %[tB1], %[mB], vcc\n\t"
-      "v_cndmask_b32 %[aB], %[n0]+3, %[aB], vcc"
-      : [mA] "+v"(mA), [aA] "+v"(argA), [mB] "+v"(mB), [aB] "+v"(argB), [tA0] "=&v"(tA0),
-        [tB0] "=&v"(tB0), [tA1] "=&v"(tA1), [tB1] "=&v"(tB1), [mk] "=&s"(maskA)
-      : [n0] "n"(4 * Q), [r0] "s"(r[0]), [r1] "s"(r[1]), [r2] "s"(r[2]), [r3] "s"(r[3]),
-        [r4] "s"(r[4]), [r5] "s"(r[5]), [r6] "s"(r[6]), [r7] "s"(r[7]),
-        [c0] "v"(c[8 * Q + 0]), [c1] "v"(c[8 * Q + 1]), [c2] "v"(c[8 * Q + 2]),
-        [c3] "v"(c[8 * Q + 3]), [c4] "v"(c[8 * Q + 4]), [c5] "v"(c[8 * Q + 5]),
-        [c6] "v"(c[8 * Q + 6]), [c7] "v"(c[8 * Q + 7])
-      : "vcc");
-}
-
-// Running state of one lane's scan: the two chains of the flat argmin.
-struct ArgminState {
-  float mA, mB;
-  int argA, argB;
-};
-
-template <int Q, int NQ, int RU, int SP>
-struct ArgminBlocks {
-  static __device__ __forceinline__ void run(ArgminState (&st)[RU], const float (&c)[RU][SP],
-                                             float8_t &r, const float *col) {
-    float8_t rn;
-#pragma unroll
-    for (int u = 0; u < RU - 1; ++u)
-      argmin_block8_shared<Q>(st[u].mA, st[u].argA, st[u].mB, st[u].argB, c[u], r);
-    argmin_block8<Q>(st[RU - 1].mA, st[RU - 1].argA, st[RU - 1].mB, st[RU - 1].argB, c[RU - 1],
-                     r, rn, col);
-    r = rn;
-    ArgminBlocks<Q + 1, NQ, RU, SP>::run(st, c, r, col);
-  }
-};
-template <int NQ, int RU, int SP>
-struct ArgminBlocks<NQ, NQ, RU, SP> {
-  static __device__ __forceinline__ void run(ArgminState (&)[RU], const float (&)[RU][SP],
-                                             float8_t &, const float *) {}
-};
-
-// First eight transition values of a column, fetched and awaited (start of a tile).
-static __device__ __forceinline__ float8_t load_col_head(const float *col) {
-  float8_t r;
-  asm volatile("s_load_dwordx8 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(r) : "s"(col) : "memory");
-  return r;
-}
 
 // ---------------------------------------------------------------------------------------
 // Level 1 of the two-level argmin (and the whole scan of the min-only pass), left to the
@@ -248,6 +88,58 @@ static __device__ __forceinline__ void scan_chunks(float &m, int &g, const float
       if (8 * q + k < SA) cm = __builtin_fminf(cm, c[8 * q + k] + r[k]);
     chunk_update<WITH_ARG>(m, g, cm, q);
   }
+}
+
+// The least sum and its source (see pair_min.h) over the first SA of SP candidates: an addition and a
+// V_MIN_F64 each, chunks of eight interleaved so that no instruction waits for the one before.  16
+// candidates with scalar transition values take a SIMD of four / eight waves 122 / 115 cycles where
+// compare and two selects took 290 / 224 (vector and scalar registers of the same instructions; an
+// addition of two vector registers would issue twice as fast).
+template <int SP, int SA>
+static __device__ __forceinline__ pair_t scan_pairs(const float (&c)[SP],
+                                                    const float *__restrict__ rc,
+                                                    const PairIndex &ix) {
+  constexpr int NQ = (SA + 7) / 8, AT = 3; // chunks of eight, chunks interleaved
+  pair_t best;
+#pragma unroll
+  for (int q0 = 0; q0 < NQ; q0 += AT) {
+    pair_t acc[AT];
+    float8_t r[AT];
+#pragma unroll
+    for (int a = 0; a < AT && q0 + a < NQ; ++a)
+      r[a] = *reinterpret_cast<const float8_t *>(rc + 8 * (q0 + a));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+#pragma unroll
+      for (int a = 0; a < AT; ++a) {
+        const int i = 8 * (q0 + a) + k;
+        if (i >= SA) break;
+        const float v = c[i] + r[a][k];
+        const pair_t p = {ix.k[k], __builtin_bit_cast(unsigned, v)};
+        acc[a] = k == 0 ? p : pair_min(acc[a], p);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < AT && q0 + a < NQ; ++a) {
+      acc[a].x |= 8u * (q0 + a);
+      best = q0 + a == 0 ? acc[a] : pair_min(best, acc[a]);
+    }
+  }
+  return best;
+}
+
+// The lowest source of chunk g (eight of them) whose sum is m, one of the chunk's sums.
+static __device__ __forceinline__ int chunk_argmin(const float *tile_lane,
+                                                   const float *__restrict__ rc, float m, int g) {
+  const float *tg = tile_lane + 8 * g * kWave; // (differs from lane to lane, as does rg)
+  const float *__restrict__ rg = rc + 8 * g;
+  const float4 fa = *reinterpret_cast<const float4 *>(rg);
+  const float4 fb = *reinterpret_cast<const float4 *>(rg + 4);
+  const float rr[8] = {fa.x, fa.y, fa.z, fa.w, fb.x, fb.y, fb.z, fb.w};
+  int kk = 7;
+#pragma unroll
+  for (int k = 6; k >= 0; --k) kk = tg[k * kWave] + rr[k] == m ? k : kk;
+  return 8 * g + kk;
 }
 
 // SP: padded strategy count (compile time).  RU: groups of 64 budget rows per wave (a lane
@@ -308,8 +200,7 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_push(
       c[u][i] = (compute && i < S && row <= E) ? srcb[(size_t)i * pitch + row] : GS_INF;
   }
 
-  float8_t rcur;
-  if (WITH_BP && compute) rcur = load_col_head(rk + (size_t)jbeg * SP);
+  const PairIndex ix;
   for (int j = jbeg; j < jend; ++j) {
     const int o = orow[j];
     const float t = trow[j];
@@ -318,18 +209,11 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_push(
       float m[RU];
       int arg[RU];
       if (WITH_BP) {
-        ArgminState st[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) st[u] = ArgminState{GS_INF, GS_INF, 0, 0};
-        ArgminBlocks<0, SP / 8, RU, SP>::run(st, c, rcur, rc);
 #pragma unroll
         for (int u = 0; u < RU; ++u) {
-          // merge the chains: candidate 2*argA (even chain) against 2*argB+1 (odd chain),
-          // the strictly smaller value wins and equal values go to the lower candidate
-          const int candA = 2 * st[u].argA, candB = 2 * st[u].argB + 1;
-          const bool takeB = (st[u].mB < st[u].mA) || (st[u].mB == st[u].mA && candB < candA);
-          m[u] = takeB ? st[u].mB : st[u].mA;
-          arg[u] = takeB ? candB : candA;
+          const pair_t p = scan_pairs<SP, SP>(c[u], rc, ix);
+          m[u] = pair_sum(p);
+          arg[u] = (int)p.x;
         }
       } else {
 #pragma unroll
@@ -386,7 +270,15 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_push(
 //            bits) and the lowest k with sum == m is the argmin 8g + k.
 // If every candidate is +inf, m stays +inf, g stays 0 and level 2 returns index 0, which
 // is what the scan gives.
+//
+// Up to 48 padded strategies the argmin is flat instead (scan_pairs, as in the push kernel): level 2
+// costs about as much as twenty candidates of level 1 and a tile's chunks are few.  Measured, 7
+// fronts, two-level / flat: S = 24 2048 tiles 85 / 77 us, 16384 416 / 378; S = 32 512 58 / 45, 16384
+// 678 / 552; S = 44 512 79 / 78, 16640 tiles (31 fronts) 4390 / 3880; S = 64 2048 269 / 275, 8192 945 /
+// 1014; S = 96 8192 1882 / 2000.
 // ---------------------------------------------------------------------------------------
+constexpr int kFlatPairs = 48; // padded strategies up to which the tile kernel's argmin is flat
+
 template <int SP, int NW, bool WITH_BP, int SA>
 __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
     const float *__restrict__ src, float *__restrict__ dst, uint8_t *__restrict__ bp,
@@ -445,53 +337,28 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
   const int jper = (S + nw - 1) / nw;
   const int jbeg = js * jper;
   const int jend = jbeg + jper < S ? jbeg + jper : S;
-  // Level 2 of a column: which of the eight candidates of chunk g attains m.  The eight
-  // transition values differ from lane to lane, so they come through the vector memory
-  // path (two 16-byte loads per lane), the eight previous-plane values from the LDS tile.
-  struct Column {
-    float4 ra, rb;
-    float m, t;
-    int g, j, o;
-  };
-  auto finish = [&](const Column &d) {
-    const float *tg = tile + (8 * d.g) * kWave + lane; // per-lane slice of the tile
-    const float rr[8] = {d.ra.x, d.ra.y, d.ra.z, d.ra.w, d.rb.x, d.rb.y, d.rb.z, d.rb.w};
-    int arg = 8 * d.g;
-#pragma unroll
-    for (int k = 7; k >= 1; --k) {
-      const float v = tg[k * kWave] + rr[k];
-      arg = (v == d.m) ? 8 * d.g + k : arg;
-    }
-    const float v0 = tg[0] + rr[0];
-    arg = (v0 == d.m) ? 8 * d.g : arg;
-    const int eo = row + d.o;
-    if (row >= low && eo <= E) {
-      // the column's base stays a scalar 64-bit address, the lanes add a 32-bit row offset
-      float *__restrict__ dj = dstb + (size_t)d.j * pitch;
-      uint8_t *__restrict__ bj = bpb + (size_t)d.j * pitch;
-      dj[(uint32_t)eo] = d.m + d.t;
-      bj[(uint32_t)eo] = (uint8_t)arg;
-    }
-  };
+  const PairIndex ix;
   for (int j = jbeg; j < jend; ++j) {
     const int o = orow[j];
     const float t = trow[j];
     if (compute) {
       const float *__restrict__ rc = rk + (size_t)j * SP;
       float m = GS_INF;
-      int g = 0;
-      scan_chunks<SP, WITH_BP, SA>(m, g, c, rc);
-      if constexpr (WITH_BP) {
-        const float *__restrict__ rg = rc + 8 * g; // per-lane slice of the column
-        Column d;
-        d.ra = *reinterpret_cast<const float4 *>(rg);
-        d.rb = *reinterpret_cast<const float4 *>(rg + 4);
-        d.m = m; d.t = t; d.g = g; d.j = j; d.o = o;
-        finish(d);
+      unsigned arg = 0;
+      if constexpr (WITH_BP && SP <= kFlatPairs) {
+        const pair_t p = scan_pairs<SP, SA>(c, rc, ix);
+        m = pair_sum(p);
+        arg = p.x;
       } else {
-        const int eo = row + o;
-        float *__restrict__ dj = dstb + (size_t)j * pitch;
-        if (row >= low && eo <= E) dj[(uint32_t)eo] = m + t;
+        int g = 0;
+        scan_chunks<SP, WITH_BP, SA>(m, g, c, rc);
+        if (WITH_BP) arg = chunk_argmin(tile + lane, rc, m, g);
+      }
+      const int eo = row + o;
+      if (row >= low && eo <= E) {
+        // the column's base stays a scalar 64-bit address, the lanes add a 32-bit row offset
+        (dstb + (size_t)j * pitch)[(uint32_t)eo] = m + t;
+        if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)arg;
       }
     }
     if (tile_start < o + low) {
@@ -561,20 +428,6 @@ static __device__ __forceinline__ float4_t mat_add(float a, const float4_t &cc) 
 static __device__ __forceinline__ float4_t mat_spread(float c) {
   const float4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
   return __builtin_amdgcn_mfma_f32_4x4x1f32(1.0f, c, z, 0, 0, 0);
-}
-
-// The lowest source of chunk g (eight of them) whose sum is m, one of the chunk's sums.
-static __device__ __forceinline__ int chunk_argmin(const float *tile_lane,
-                                                   const float *__restrict__ rc, float m, int g) {
-  const float *tg = tile_lane + 8 * g * kWave; // (differs from lane to lane, as does rg)
-  const float *__restrict__ rg = rc + 8 * g;
-  const float4 fa = *reinterpret_cast<const float4 *>(rg);
-  const float4 fb = *reinterpret_cast<const float4 *>(rg + 4);
-  const float rr[8] = {fa.x, fa.y, fa.z, fa.w, fb.x, fb.y, fb.z, fb.w};
-  int kk = 7;
-#pragma unroll
-  for (int k = 6; k >= 0; --k) kk = tg[k * kWave] + rr[k] == m ? k : kk;
-  return 8 * g + kk;
 }
 
 // Up to how many listed sources the short scan is the faster one, the bounds being paid for.
@@ -2227,14 +2080,20 @@ static void launch_push(const Shape &s, const Workspace &w, int l, const float *
                         void *bp_l, hipStream_t st) {
   int jsplit, wpb;
   push_launch_shape(s, jsplit, wpb);
-  // Row groups per wave.  Measured: they pay only for the min-only pass (5 % on the outer
-  // search batch), where the shared scalar loads and loop overhead are a large part of a
-  // short column; the flat argmin is bound by its own instruction count either way and
-  // loses occupancy to the extra registers.  Used while the batch still yields at least
-  // eight waves per SIMD.  The knob "row_groups" overrides.
+  // Row groups per wave share a column's scalar loads, its T and O and the loop; they cost
+  // registers, so they need a batch that still fills the SIMDs.  Measured, 7 fronts, us at one /
+  // two / four groups: with backpointers S = 8 4096 tiles 50 / 46 / 55, 16384 124 / 107 / 105; S = 16
+  // 8192 137 / 135 / 142, 16384 233 / 215 / 215; S = 24 16384 339 / 348 / 356, 32768 893 / 814 / 730,
+  // outer search (2048 instances) 6160 / 5895 / 5620; S = 32 16384 545 / 541, 32768 1222 / 1159; S =
+  // 44 32768 1850 / 1953.  Min-only 5 % on the outer search.  The knob "row_groups" overrides.
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.Bc * jsplit;
   int ru = s.tune.row_groups;
-  if (ru < 1) ru = bp_l ? 1 : (tiles >= 4 * 8192 ? 4 : (tiles >= 2 * 8192 ? 2 : 1));
+  if (ru < 1) {
+    if (!bp_l) ru = tiles >= 4 * 8192 ? 4 : (tiles >= 2 * 8192 ? 2 : 1);
+    else if (SP <= 16) ru = tiles >= 24576 ? 4 : 2;
+    else if (SP <= 32) ru = tiles >= 24576 ? 4 : 1; // (two where there is no form of four)
+    else ru = 1;
+  }
   if constexpr (SP <= 24) {
     if (ru >= 4) return launch_push_ru<SP, 4>(s, w, l, src, dst, bp_l, jsplit, wpb, st);
   }
@@ -2374,11 +2233,12 @@ bool fronts_shape_ok(const Shape &s) {
 //     292; and with one instance per XCD 44 to 162 strategies, 65 tiles, 174 / 204 .. 261 / 287, 24,
 //     94 tiles, 139 / 165 (the tiles of two fronts just about fill the XCD)
 // load - 3/4 of an even spread's load is what the uneven spread and the longer front cost; the
-// limits are where that eats the launches saved up.  (Under eight layers the form's two small
-// launches cost that much: left to batches that fill the XCDs evenly.)
+// limits are where that eats the launches saved up.  Under eight layers, where the form's two small
+// launches weigh more and either way is a matter of a few launches, batches that fill the XCDs
+// evenly take it.
 bool fronts_pay(const Shape &s, bool with_bp) {
   const long long tiles = (s.M + kWave) / kWave, q = (s.B + 7) / 8;
-  if (s.L < 8 && s.B % 8 != 0 && s.B < 64) return false;
+  if (s.L < 8) return s.B % 8 == 0 || s.B >= 64;
   if (!with_bp && q == 1 && tiles >= 64 && tiles <= 110) return false;
   const long long limit = with_bp ? (s.SP <= 48 ? 140 : s.SP <= 96 ? 92 : s.SP <= 128 ? 72 : 36)
                                   : (s.SP <= 96 ? 145 : s.SP <= 128 ? 120 : 75);
@@ -2593,8 +2453,9 @@ static void launch_bound_as(const Shape &s, const Workspace &w, int l, const flo
 // solves of 12 layers, layer times of 1 to 10 and transition costs of up to 1 / 2 / 4 / 10 (how
 // far the bounds reach depends on that ratio; nothing is left out in the last one, which is also
 // what tables with a forbidden target per source take), new / old time:
-//   with backpointers  S = 30, 16 tiles 0.83 / 0.84 / 0.93 / 1.03, 256 tiles 0.86 / 0.92 / 1.02 /
-//     1.03 (S = 25: 1.10, not taken); S = 44, 256 tiles 0.81 / 0.87 / 0.93 / 0.93 (520 tiles of the
+//   with backpointers  S = 29 to 32 against the tile kernel's flat argmin, 8 to 512 tiles 0.96 to 1.14 /
+//     1.03 to 1.35 / 1.28 to 1.47 / 1.28 to 1.39: not taken any more, but for the shortest searches (16
+//     tiles, or three an instance: 1.0 to 1.1 / 1.05 to 1.35), whose kernel is as it was; S = 44, 256 tiles 0.81 / 0.87 / 0.93 / 0.93 (520 tiles of the
 //     encoder-decoder batch lose: not taken); S = 64, 128 tiles 0.84 / 1.01 / 1.03 / 1.04, 512 tiles
 //     0.79 / 0.92 / 0.94 / 0.93, 1024 tiles 0.92 / 1.11 / 1.10 / 1.10 (not taken); S = 80, 256 tiles
 //     0.79 / 0.92 / 0.95 / 0.95, 512 tiles 0.91 / 1.12 / 1.12 / 1.11 (not taken: ten waves of eight
@@ -2615,7 +2476,8 @@ static void launch_bound_as(const Shape &s, const Workspace &w, int l, const flo
 static bool bound_pays(const Shape &s, bool with_bp) {
   const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
   switch (s.SP) {
-    case 32: return s.S > 28 && tiles <= 256;
+    case 32:
+      return s.S > 28 && tiles <= 256 && (!with_bp || tiles <= 16 || s.M < 3 * kWave);
     case 48: return tiles <= 256;
     case 64: return tiles <= 512;
     case 96: return s.S > 84 || tiles <= (with_bp ? 256 : 512) || (!with_bp && tiles >= 2048);
@@ -2666,18 +2528,22 @@ const char *launch_dp_layer(const Shape &s, const Workspace &w, int l, const flo
     return "k_dp_bound";
   }
   // What the bounded kernel leaves (see bound_pays), and forced kernels.
-  // Which register-tiled kernel: measured on MI355X, the LDS-staged two-level kernel wins
-  // from 48 padded strategies up when backpointers are wanted (its argmin costs about 2.3
-  // instead of 4 vector instructions per relaxation) and for 48..64 without them; the
-  // plain push kernel wins for small S (few chunks, relatively more fixed work per tile)
-  // and for the min-only pass at S >= 96.  The context flags (or the knob "kernel" = 1 | 2) force one.
-  bool use_tile = bp_l ? tsp >= 48 : (tsp >= 48 && tsp <= 64);
-  // Small S: the push kernel wins on big batches (outer search: 2048 instances), but while
-  // the batch has few tiles a front is bound by the length of one wave's work, and the
-  // tile kernel's four waves per tile shorten it (measured crossover: about 16 K tiles with
-  // backpointers, 4 K without).
+  // Which register-tiled kernel.  The LDS-staged one splits a tile's targets among four waves and
+  // so shortens a front of few tiles; the push kernel, one wave per tile or more, has no barrier
+  // and no second copy of the tile.  Measured, 7 fronts, us, tile / push kernel: with backpointers
+  // S = 8 2048 tiles 38 / 38, 4096 59 / 46; S = 16 4096 85 / 87, 8192 152 / 135; S = 24 8192 207 / 209,
+  // 16384 373 / 339; S = 32 8192 295 / 285, 16384 552 / 541; S = 44 16640 (31 fronts) 3880 / 3979,
+  // 20480 1245 / 1217, 32768 2135 / 1850; S = 64 4096 456 / 478, 8192 930 / 898, 16384 1971 / 1760; S =
+  // 96 always tile (8192 1890 / 2200).  Min-only S <= 32 about 4 K; S = 44 8192 359 / 385, 12800 543 /
+  // 537, 32768 1626 / 1412; S = 64 8192 650 / 666, 16384 1311 / 1192; S >= 96 always push.  The
+  // context flags (or the knob "kernel" = 1 | 2) force one.
   const long long tile_inst = (long long)((s.M + kWave) / kWave) * s.Bc;
-  if (tsp != 0 && tsp <= 32) use_tile = tile_inst <= (bp_l ? 16384 : 4096);
+  bool use_tile;
+  if (bp_l)
+    use_tile = tsp >= 96 || tile_inst <= (tsp <= 8 ? 3000 : tsp <= 16 ? 6000 : tsp <= 32 ? 12000
+                                          : tsp <= 48 ? 20000 : 6000);
+  else
+    use_tile = tsp < 96 && tile_inst <= (tsp <= 32 ? 4096 : 12000);
   // The LDS-streamed kernel (made for more than 128 strategies) also wins below that where
   // the register-tiled ones run out of registers (measured, 7 fronts, ms: S = 128, 8 x 16385
   // rows: 0.79 against 0.85 with backpointers, 0.62 against 0.71 without; 96 padded strategies up

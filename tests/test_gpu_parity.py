@@ -1687,6 +1687,42 @@ def test_bounded_kernel_votes_start_afresh(gs, oracle_mod, S):
             assert_same(got, oracle_batch(oracle_mod, w), w, f"replay {rep}")
 
 
+@pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=4),
+                                   dict(kernel=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
+@pytest.mark.parametrize("S", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 40, 41, 44, 45, 48])
+def test_flat_argmin_of_pairs(gs, oracle_mod, S, knobs):
+    """Sum and index as one double: ties within and across chunks of eight, subnormal and zero sums,
+    sums that overflow, forbidden transitions up to whole columns, tile edges; planes and
+    backpointers whole."""
+    binding, runner = gs
+    B, L, M, K = 3, 5, 130, 2
+    w = random_tables(f"pairs{S}", B, L, S, M, K=K, seed=S + 900, budget=np.array([M, 127, 64], np.int32),
+                      o_hi=40)
+    w.T[0] = np.floor(w.T[0] / 4)                                   # many equal sums
+    w.R[0] = np.floor(w.R[0])
+    w.T[1, ::2] *= np.float32(1e-42)                                # subnormal
+    w.R[1] = np.where(w.R[1] > 1.4, np.float32(np.inf), w.R[1] * np.float32(1e-41))
+    w.T[2] = np.where(w.T[2] > 8, np.float32(3e38), w.T[2])         # overflow to +inf
+    w.R[1, :, S // 2] = np.inf                                      # no way into one target
+    dw = runner.DeviceWorkload(w)
+    ref = oracle_batch(oracle_mod, w)
+    with runner.make_context(w, flags=binding.GSEARCH_FLAG_KEEP_PLANES) as ctx:
+        ctx.gsearch_set_knob("small", 0)
+        for name, value in knobs.items():
+            ctx.gsearch_set_knob(name, value)
+        got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all"))
+        got["data_status"] = ctx.gsearch_data_status()
+        assert ctx.gsearch_forward_kernel() == ("k_dp_push" if knobs["kernel"] == 1 else "k_dp_tile")
+        C, bp = ctx.gsearch_export_planes(want_bp=True)
+        C, bp = C.cpu().numpy(), bp.cpu().numpy()
+    assert_same(got, ref, w, f"S={S} {knobs}")
+    for b in range(B):
+        E = int(w.budget[b])
+        one = oracle_mod.solve(w.T[b], w.O[b], w.R, w.r_index[b], E, want_planes=True)
+        assert np.array_equal(bits(C[b, :, :E + 1, :]), bits(one["C"])), (S, b)
+        assert np.array_equal(bp[b, :, :E + 1, :], one["bp"].astype(np.int32)), (S, b)
+
+
 @pytest.mark.parametrize("kernel,name", [(1, "k_dp_push"), (2, "k_dp_tile"), (3, "k_dp_wide")])
 @pytest.mark.parametrize("S", [49, 64, 80, 96, 100, 128])
 @pytest.mark.parametrize("flags", [0, 0x4])
