@@ -1817,105 +1817,185 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_generic(
 // Whole forward pass of a SMALL instance in one launch (latency path).
 //
 // One workgroup per instance runs layer 0 .. L-1 back to back; the two ping-pong planes
-// live in LDS ([s][e], pitch a multiple of 64), so a layer front costs one workgroup
-// barrier instead of a kernel launch.  The transition pool and the instance's T, O and
-// r_index rows are copied to LDS first, so that no layer waits for a chain of scalar loads.
-// Threads are laid out as (budget row) x (group of target strategies).  A thread owns a
-// SOURCE row e' ("push" form): it reads C[l-1][e'][.] from LDS once per layer, scans it
-// against the staged column of every target sj of its group (all lanes of a wave share sj,
-// so those are broadcast LDS reads), and stores the result at row e' + O[l][sj] of the next
-// plane; the rows e < O[l][sj], which no source row reaches, are filled with +inf by the
-// thread that owns that row.  Every row 0..E of every target is written exactly once.
-// Flat strict-"<" scan, four candidates at a time up to S; backpointers go to HBM as in the
-// other kernels.  The last plane (or every plane when all are kept) is copied to the HBM
-// workspace so that the final reductions, the budget curve and the plane-based backtrace
-// read what they always read.
+// live in LDS ([s][row], pitch a multiple of 64), so a layer front costs one workgroup
+// barrier instead of a kernel launch.  The transition pool and the instance's T, O, r_index and
+// least-memory rows are copied to LDS first, so that no layer waits for global memory.
+// Threads are laid out as (row) x (group of target strategies).  A thread owns a SOURCE row ("push"
+// form): it reads C[l-1][row][.] from LDS once per layer, scans it against the column of every
+// target of its group (all lanes of a wave share the target) and stores the result O[l][sj] rows
+// higher in the next plane; rows that no source row reaches are filled with +inf by their owner.
+// Only rows that matter are held (unless kept planes are exported whole): row p of plane l is
+// budget row p + (least memory of layers 0..l), up to E less the least memory of the later layers,
+// the same number in every layer, so a result moves up by O[l][sj] less the layer's least memory.
+// A sum and its source are one double (pair_min.h).  Backpointers go to HBM as in the other
+// kernels.  The last plane (or every plane when all are kept) is written to the HBM workspace too,
+// so that the final reductions, the budget curve and the plane-based backtrace read what they
+// always read.
+//
+// Bound by the vector ALU of the one compute unit and, with many targets a thread, by LDS: a column
+// read by all lanes costs a wave 2 cycles a value like any other, so while a thread has few targets
+// their columns stay in its registers and are read again only when the layer's transition matrix
+// is another (12 strategies, 256 bins, 23 fronts: 36.6 -> 34.2 us).  Measured, 23 fronts, before (flat
+// compare and two selects, every row, sources padded to a multiple of eight) / now: 12 strategies
+// 256 bins 63 / 34 us, 768 143 / 79; 8 strategies 512 bins 66 / 33; 16 / 256 80 / 48; 24 / 128 98 / 50,
+// 24 / 384 224 / 108; 32 / 64 188 / 48.
 // ---------------------------------------------------------------------------------------
-template <int SP>
+template <int SQ, bool WITH_BP>
+static __device__ __forceinline__ void small_scan(const float (&c)[SQ], const float (&r)[SQ],
+                                                  const PairIndex &ix, float &m, unsigned &arg) {
+  if constexpr (WITH_BP) {
+    pair_t best;
+#pragma unroll
+    for (int q = 0; q < (SQ + 7) / 8; ++q) {
+      pair_t a[2];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int i = 8 * q + k;
+        if (i >= SQ) break;
+        const pair_t p = {ix.k[k], __builtin_bit_cast(unsigned, c[i] + r[i])};
+        a[k & 1] = k < 2 ? p : pair_min(a[k & 1], p);
+      }
+      a[0] = pair_min(a[0], a[1]);
+      a[0].x |= 8u * q;
+      best = q == 0 ? a[0] : pair_min(best, a[0]);
+    }
+    m = pair_sum(best);
+    arg = best.x;
+  } else {
+    m = __builtin_fminf(c[0] + r[0], c[1] + r[1]);
+#pragma unroll
+    for (int i = 2; i < SQ; i += 2) m = __builtin_fminf(__builtin_fminf(m, c[i] + r[i]), c[i + 1] + r[i + 1]);
+    arg = 0;
+  }
+}
+
+// SQ: sources scanned, S rounded up to 4.  PER: most targets of a thread whose transition columns
+// are kept in its registers; 0: any number of targets, the columns read from LDS.
+template <int SQ, int PER, bool WITH_BP>
 __global__ __launch_bounds__(1024) void k_dp_small(
     float *__restrict__ planes, uint8_t *__restrict__ bp, const float *__restrict__ Tq,
     const int32_t *__restrict__ Oq, const float *__restrict__ Rt,
-    const int32_t *__restrict__ ridx, const int32_t *__restrict__ budget, int B, int L, int S,
-    int K, int pitch, int keep_all, int last_plane) {
-  extern __shared__ float lds[]; // two planes of S * pitch floats, then the staged tables
+    const int32_t *__restrict__ ridx, const int32_t *__restrict__ budget,
+    const int32_t *__restrict__ minO, const int32_t *__restrict__ lowsum, int B, int L, int S,
+    int SP, int K, int pitch, int keep_all, int keep_rows, int last_plane) {
+  extern __shared__ __align__(16) float lds[]; // two planes of S * pitch floats, then the tables
+  constexpr int SMIN = SQ - 3;                 // S is at least this
   const int b = blockIdx.x;
-  float *Rl = lds + (size_t)2 * S * pitch;               // [K][SP][SP]
-  float *Tl = Rl + (size_t)K * SP * SP;                  // [L][SP]
-  int *Ol = reinterpret_cast<int *>(Tl + (size_t)L * SP); // [L][SP]
-  int *kl = Ol + (size_t)L * SP;                         // [L]
+  float *Rl = lds + (size_t)2 * S * pitch;                      // [K][SP][SP]
+  float2 *TO = reinterpret_cast<float2 *>(Rl + (size_t)K * SP * SP); // [L][SP]: T, O
+  int2 *kl = reinterpret_cast<int2 *>(TO + (size_t)L * SP);     // [L]: matrix, least O
   for (int x = threadIdx.x; x < K * SP * SP; x += blockDim.x) Rl[x] = Rt[x];
-  for (int x = threadIdx.x; x < L * SP; x += blockDim.x) {
-    Tl[x] = Tq[(size_t)b * L * SP + x];
-    Ol[x] = Oq[(size_t)b * L * SP + x];
-  }
-  for (int x = threadIdx.x; x < L; x += blockDim.x) kl[x] = ridx[(size_t)b * L + x];
-  __syncthreads();
+  for (int x = threadIdx.x; x < L * SP; x += blockDim.x)
+    TO[x] = make_float2(Tq[(size_t)b * L * SP + x],
+                        __builtin_bit_cast(float, Oq[(size_t)b * L * SP + x]));
+  for (int x = threadIdx.x; x < L; x += blockDim.x)
+    kl[x] = make_int2(ridx[(size_t)b * L + x], keep_rows ? 0 : minO[(size_t)b * L + x]);
   const int E = budget[b];
-  const int rows64 = (E + 1 + kWave - 1) / kWave * kWave; // threads along e
-  const int groups = (int)blockDim.x / rows64;             // >= 1 by the launch condition
-  const int e = (int)threadIdx.x % rows64;
-  const int jg = (int)threadIdx.x / rows64;
-  const bool active = jg < groups && e <= E;
+  // The rows that matter: those of plane l from base = the least memory of layers 0..l up to E
+  // less the least memory of the later layers, always `rows` of them.
+  const int rows = keep_rows ? E + 1 : E + 1 - lowsum[(size_t)b * L + L - 1];
+  const int rows64 = rows > 0 ? (rows + kWave - 1) / kWave * kWave : kWave; // threads along them
+  int groups = (int)blockDim.x / rows64;                    // >= 1 by the launch condition
+  groups = groups < S ? groups : S;
+  const int p = (int)threadIdx.x % rows64;
+  const int jg = wave_uniform((int)threadIdx.x / rows64);
+  const bool active = jg < groups && p < rows;
   const size_t plane_elems_all = (size_t)B * S * pitch;
   const size_t plane_off = (size_t)b * S * pitch;
   float *cur = lds;
   float *nxt = lds + (size_t)S * pitch;
-
-  if (active)
+  __syncthreads();
+  int base = kl[0].y;
+  if (active) {
+    float *g = planes + plane_off + base;
     for (int s0 = jg; s0 < S; s0 += groups) {
-      const float v = (e >= Ol[s0]) ? Tl[s0] : GS_INF;
-      cur[s0 * pitch + e] = v;
-      if (keep_all || L == 1) planes[plane_off + (size_t)s0 * pitch + e] = v;
+      const float2 to = TO[s0];
+      const float v = (p + base >= __builtin_bit_cast(int, to.y)) ? to.x : GS_INF;
+      cur[s0 * pitch + p] = v;
+      if (keep_all || L == 1) g[(size_t)s0 * pitch + p] = v;
     }
+  }
+  const PairIndex ix;
+  float rr[PER > 0 ? PER : 1][SQ];
+  int kr = -1;
+  auto column = [&](float (&r)[SQ], const float *rc) {
+#pragma unroll
+    for (int i = 0; i < SQ; i += 4) {
+      const float4 q = *reinterpret_cast<const float4 *>(rc + i);
+      r[i] = q.x;
+      r[i + 1] = q.y;
+      r[i + 2] = q.z;
+      r[i + 3] = q.w;
+    }
+  };
   for (int l = 1; l < L; ++l) {
     __syncthreads();
-    const float *rk = Rl + (size_t)kl[l] * SP * SP;
-    float *gplane = planes + (keep_all ? (size_t)l * plane_elems_all : (size_t)last_plane * plane_elems_all) + plane_off;
-    uint8_t *gbp = bp ? bp + (size_t)(l - 1) * plane_elems_all + plane_off : nullptr;
+    const int2 kn = kl[l];
+    const int k = wave_uniform(kn.x), least = wave_uniform(kn.y);
+    const float *rk = Rl + (size_t)k * SP * SP;
+    const int nbase = base + least;
+    float *gplane = planes + (keep_all ? (size_t)l * plane_elems_all : (size_t)last_plane * plane_elems_all) +
+                    plane_off + nbase;
+    uint8_t *gbp = WITH_BP ? bp + (size_t)(l - 1) * plane_elems_all + plane_off + nbase : nullptr;
     const bool to_global = keep_all || l == L - 1;
     if (active) {
-      float c[SP];
+      float c[SQ];
 #pragma unroll
-      for (int i = 0; i < SP; ++i) c[i] = i < S ? cur[i * pitch + e] : GS_INF;
-      for (int j = jg; j < S; j += groups) {
-        const int o = Ol[l * SP + j];
-        const float t = Tl[l * SP + j];
-        const float *rc = rk + (size_t)j * SP;
-        float m = GS_INF;
-        int arg = 0;
-#pragma unroll
-        for (int i0 = 0; i0 < SP; i0 += 4) {
-          if (i0 < S) { // uniform: whole chunks of padding are skipped
-            const float4 r = *reinterpret_cast<const float4 *>(rc + i0);
-            const float rr[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const float v = c[i0 + k] + rr[k];
-              if (v < m) { m = v; arg = i0 + k; }
-            }
-          }
+      for (int i = 0; i < SQ; ++i) c[i] = i < SMIN || i < S ? cur[i * pitch + p] : GS_INF;
+      auto target = [&](int j, const float2 &to, const float (&r)[SQ]) {
+        float m;
+        unsigned arg;
+        small_scan<SQ, WITH_BP>(c, r, ix, m, arg);
+        const int shift = __builtin_bit_cast(int, to.y) - least;
+        const int pt = p + shift;
+        if (pt < rows) {
+          const float out = m + to.x;
+          nxt[j * pitch + pt] = out;
+          if (to_global) (gplane + j * pitch)[(unsigned)pt] = out;
+          if (WITH_BP) (gbp + j * pitch)[(unsigned)pt] = (uint8_t)arg;
         }
-        const int eo = e + o;
-        if (eo <= E) {
-          const float out = m + t;
-          nxt[j * pitch + eo] = out;
-          if (to_global) gplane[(size_t)j * pitch + eo] = out;
-          if (gbp) gbp[(size_t)j * pitch + eo] = (uint8_t)arg;
+        if (p < shift) { // no source row reaches this target row
+          nxt[j * pitch + p] = GS_INF;
+          if (to_global) (gplane + j * pitch)[(unsigned)p] = GS_INF;
+          if (WITH_BP && keep_rows) (gbp + j * pitch)[(unsigned)p] = 0;
         }
-        if (e < o) { // no source row reaches this target row
-          nxt[j * pitch + e] = GS_INF;
-          if (to_global) gplane[(size_t)j * pitch + e] = GS_INF;
-          if (gbp) gbp[(size_t)j * pitch + e] = 0;
+      };
+      if constexpr (PER > 0) {
+        float2 to[PER];
+#pragma unroll
+        for (int x = 0; x < PER; ++x) to[x] = TO[l * SP + (jg + x * groups < S ? jg + x * groups : jg)];
+        if (k != kr) { // (uniform)
+          kr = k;
+#pragma unroll
+          for (int x = 0; x < PER; ++x)
+            column(rr[x], rk + (size_t)(jg + x * groups < S ? jg + x * groups : jg) * SP);
+        }
+#pragma unroll
+        for (int x = 0; x < PER; ++x)
+          if (jg + x * groups < S) target(jg + x * groups, to[x], rr[x]); // (uniform)
+      } else {
+        for (int j = jg; j < S; j += groups) {
+          float r[SQ];
+          column(r, rk + (size_t)j * SP);
+          target(j, TO[l * SP + j], r);
         }
       }
     }
+    base = nbase;
     float *tmp = cur; cur = nxt; nxt = tmp;
+  }
+  // the last plane's rows that no plan reaches (all of them when no plan fits)
+  if (!keep_rows) {
+    float *g = planes + (keep_all || L == 1 ? (size_t)(L - 1) : (size_t)last_plane) * plane_elems_all + plane_off;
+    const int below = rows > 0 ? base : E + 1;
+    for (int s0 = (int)threadIdx.x >> 6; s0 < S; s0 += (int)blockDim.x >> 6)
+      for (int e = threadIdx.x & 63; e < below; e += kWave) g[(size_t)s0 * pitch + e] = GS_INF;
   }
 }
 
-// LDS bytes of the staged tables: transition pool, T and O rows, r_index row
+// LDS bytes of the staged tables: transition pool, T and O rows, r_index and least-memory rows
 static size_t small_table_bytes(const Shape &s) {
-  return sizeof(float) * ((size_t)s.K * s.SP * s.SP + (size_t)2 * s.L * s.SP + (size_t)s.L);
+  return sizeof(float) * ((size_t)s.K * s.SP * s.SP + (size_t)2 * s.L * s.SP + (size_t)2 * s.L);
 }
 
 // The latency path applies when an instance's budget rows fit one workgroup, its two planes
@@ -1927,25 +2007,19 @@ bool small_path_applies(const Shape &s, bool with_bp) {
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.B;
   if (tiles > 2048) return false;
   // One workgroup per instance means one compute unit per instance, so the one-launch kernel
-  // wins only while a thread's share of a layer front is short.  A thread owns a budget row
-  // and every groups-th target strategy: per = ceil(S / groups) scans of S candidates, and
-  // the workgroup's waves share one compute unit.  Measured per layer (24 layers, 1 and 64
-  // instances, S = 8..44, M = 64..1000), in microseconds:
-  //   one launch  0.9 + 0.0021 * per * S * max(waves, 14)
-  //   tile kernel 1.6 + 0.18 S per launch with backpointers, 1.5 + 0.13 S without
-  // e.g. S = 12, M = 256 (per = 4, 15 waves): 62 us against 88 (77 min-only) for 23 fronts;
-  // S = 8, M = 512: 66 against 74; S = 24, M = 128: 100 against 123 (100); S = 32, M = 64: 121
-  // against 157 (124); S = 16, M = 512: 185 against 105.  The knob "small" = 0 / 1 (tuning)
-  // switches the path off / on wherever it fits.
+  // wins only while a layer front is short for one.  Measured per layer (24 layers, 1 and 64
+  // instances, S = 4..32, M = 64..1000), in microseconds, within a tenth or so:
+  //   one launch  0.5 + 0.00078 tiles S (S + 8) with backpointers, 0.00066 without
+  //   tile kernel 1.9 + 0.115 S per launch
+  // e.g. 23 fronts, us, tile / one launch: S = 8, 1000 bins 70 / 51; S = 12, 768 83 / 79, 1000 83 / 91
+  // (min-only 82 / 78); S = 16, 512 89 / 76; S = 20, 384 103 / 87, 512 104 / 102; S = 24, 256 101 / 77, 384
+  // 106 / 108 (min-only 105 / 94); S = 32, 256 138 / 118.  The knob "small" = 0 / 1 (tuning) switches the
+  // path off / on wherever it fits.
   const int forced = s.tune.small;
   if (forced == 0 || forced == 1) return forced == 1;
-  const int rows64 = (s.M + 1 + kWave - 1) / kWave * kWave;
-  const int groups = s.S < 1024 / rows64 ? s.S : 1024 / rows64;
-  const int per = (s.S + groups - 1) / groups;
-  const int waves = groups * rows64 / kWave;
-  const double one_launch = 0.9 + 0.0021 * per * s.S * (waves > 14 ? waves : 14);
-  const double per_front = with_bp ? 1.6 + 0.18 * s.S : 1.5 + 0.13 * s.S;
-  return one_launch <= per_front;
+  const double rounds = (s.B + 255) / 256; // (256 compute units)
+  const double front = (double)((s.M + kWave) / kWave) * s.S * (s.S + 8);
+  return rounds * (0.5 + (with_bp ? 0.00078 : 0.00066) * front) <= 1.9 + 0.115 * s.S;
 }
 
 // More than 64 KB of dynamic LDS per workgroup has to be asked for, per kernel: the context's
@@ -1964,28 +2038,50 @@ static void lds_opt_in(const void *kernel, size_t lds, LdsGrants *g) {
   }
 }
 
-void launch_dp_small(const Shape &s, const Workspace &w, bool keep_all, int last_plane,
-                     hipStream_t st) {
+template <int SQ, int PER>
+static void launch_small_as(const Shape &s, const Workspace &w, int threads, bool keep_all,
+                            bool keep_rows, int last_plane, hipStream_t st) {
   const size_t lds = (size_t)2 * s.S * s.pitch * sizeof(float) + small_table_bytes(s);
+  const void *fn = w.bp ? (const void *)k_dp_small<SQ, PER, true> : (const void *)k_dp_small<SQ, PER, false>;
+  if (lds > 64 * 1024) lds_opt_in(fn, lds, s.grants);
+  if (w.bp)
+    hipLaunchKernelGGL((k_dp_small<SQ, PER, true>), dim3(s.B), dim3(threads), lds, st, w.planes,
+                       (uint8_t *)w.bp, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.minO, w.lowsum, s.B, s.L,
+                       s.S, s.SP, s.K, s.pitch, keep_all ? 1 : 0, keep_rows ? 1 : 0, last_plane);
+  else
+    hipLaunchKernelGGL((k_dp_small<SQ, PER, false>), dim3(s.B), dim3(threads), lds, st, w.planes,
+                       (uint8_t *)nullptr, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.minO, w.lowsum, s.B, s.L,
+                       s.S, s.SP, s.K, s.pitch, keep_all ? 1 : 0, keep_rows ? 1 : 0, last_plane);
+}
+
+template <int SQ>
+static void launch_small_sq(const Shape &s, const Workspace &w, bool keep_all, bool keep_rows,
+                            int last_plane, hipStream_t st) {
   const int rows64 = (s.M + 1 + kWave - 1) / kWave * kWave;
-  int threads = (1024 / rows64) * rows64; // whole groups of target strategies
-  const int useful = ((s.S < 1024 / rows64) ? s.S : 1024 / rows64) * rows64;
-  if (useful < threads) threads = useful;
-#define GS_SMALL(SPV)                                                                     \
-  do {                                                                                    \
-    if (lds > 64 * 1024) lds_opt_in((const void *)k_dp_small<SPV>, lds, s.grants);        \
-    hipLaunchKernelGGL((k_dp_small<SPV>), dim3(s.B), dim3(threads), lds, st, w.planes,    \
-                       (uint8_t *)w.bp, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, s.B, s.L, s.S, \
-                       s.K, s.pitch, keep_all ? 1 : 0, last_plane);                       \
-  } while (0)
-  switch (s.SP) { // small_path_applies() admits no other size
-    case 8: GS_SMALL(8); break;
-    case 16: GS_SMALL(16); break;
-    case 24: GS_SMALL(24); break;
-    case 32: GS_SMALL(32); break;
+  const int groups = s.S < 1024 / rows64 ? s.S : 1024 / rows64;
+  const int per = (s.S + groups - 1) / groups;
+  // (more than groups * rows64: the instance may have fewer rows that matter, and more groups then)
+  const int threads = s.S * rows64 < 1024 ? s.S * rows64 : 1024;
+  // targets whose columns fit the registers of sixteen waves
+  constexpr int KEEP = SQ <= 12 ? 4 : SQ <= 16 ? 3 : SQ <= 24 ? 2 : 0;
+  if (KEEP > 0 && per <= KEEP)
+    return launch_small_as<SQ, KEEP>(s, w, threads, keep_all, keep_rows, last_plane, st);
+  launch_small_as<SQ, 0>(s, w, threads, keep_all, keep_rows, last_plane, st);
+}
+
+void launch_dp_small(const Shape &s, const Workspace &w, bool keep_all, bool keep_rows,
+                     int last_plane, hipStream_t st) {
+  switch ((s.S + 3) / 4) { // small_path_applies() admits no more
+    case 1: launch_small_sq<4>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 2: launch_small_sq<8>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 3: launch_small_sq<12>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 4: launch_small_sq<16>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 5: launch_small_sq<20>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 6: launch_small_sq<24>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 7: launch_small_sq<28>(s, w, keep_all, keep_rows, last_plane, st); break;
+    case 8: launch_small_sq<32>(s, w, keep_all, keep_rows, last_plane, st); break;
     default: break;
   }
-#undef GS_SMALL
 }
 
 int tuned_sp_for(int S) {

@@ -381,7 +381,7 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
     // latency path: layer 0 and every layer front in one launch, planes in LDS
     cur = keep ? s.L - 1 : ((s.L - 1) & 1);
     if (timing && hipEventRecord(ctx->ev_begin, st) != hipSuccess) return GSEARCH_ERR_HIP;
-    gs::launch_dp_small(s, w, keep, cur, st);
+    gs::launch_dp_small(s, w, keep, (c.flags & GSEARCH_FLAG_KEEP_PLANES) != 0, cur, st);
     ctx->forward_kernel = "k_dp_small";
     ctx->groups_used = 1;
   } else if (use_classes && fronts_per_launch(ctx, s, with_bp) > 0) {

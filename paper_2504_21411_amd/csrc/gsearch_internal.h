@@ -164,8 +164,9 @@ bool bound_applies(const Shape &s, bool with_bp);
 bool bound_needs_table(const Shape &s);
 // Single-launch forward pass for small instances (includes layer 0); see dp_kernels.hip.
 bool small_path_applies(const Shape &s, bool with_bp);
-void launch_dp_small(const Shape &s, const Workspace &w, bool keep_all, int last_plane,
-                     hipStream_t st);
+// keep_rows: the rows that lead to no result are wanted as well.
+void launch_dp_small(const Shape &s, const Workspace &w, bool keep_all, bool keep_rows,
+                     int last_plane, hipStream_t st);
 void launch_final(const Shape &s, const Workspace &w, const float *last_plane,
                   float *best_cost, int32_t *best_s, float *final_row, int32_t *best_instance,
                   hipStream_t st);

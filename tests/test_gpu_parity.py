@@ -1687,6 +1687,47 @@ def test_bounded_kernel_votes_start_afresh(gs, oracle_mod, S):
             assert_same(got, oracle_batch(oracle_mod, w), w, f"replay {rep}")
 
 
+@pytest.mark.parametrize("S,M", [(1, 70), (3, 900), (4, 63), (5, 500), (8, 1000), (9, 64), (12, 257), (12, 500),
+                                 (13, 300), (16, 130), (17, 128), (20, 400), (21, 192), (24, 90), (24, 300),
+                                 (28, 100), (29, 65), (32, 64), (32, 250)])
+def test_one_launch_kernel_forms(gs, oracle_mod, S, M):
+    """Both forms of the one-launch kernel (columns in registers, columns from LDS) over its strategy
+    counts: instances whose rows that matter are all, few, one or none of their budget's, layers that
+    share a transition matrix and layers that do not, ties; costs, plans, the budget curve and, where
+    kept, whole planes and backpointers."""
+    binding, runner = gs
+    B, L = 5, 7
+    budget = np.array([M, M - 1, 2 * M // 3, M, M // 2], np.int32)
+    w = random_tables(f"smallforms{S}", B, L, S, M, K=3, seed=7 * S + M, budget=budget, o_hi=max(1, M // L))
+    w.T[0] = np.floor(w.T[0] / 4)
+    w.R[0] = np.floor(w.R[0])
+    w.r_index[1] = 0
+    w.O[1] += M // (2 * L)                             # half of the rows cannot matter
+    w.O[3, :L - 1] = M // L                            # one row matters, or a few
+    w.O[3, L - 1] = M - (L - 1) * (M // L)
+    w.O[4] = M // L + 1                                # nothing fits half the budget
+    ref = oracle_batch(oracle_mod, w)
+    assert np.isfinite(ref["best_cost"][3]) and np.isinf(ref["best_cost"][4])
+    dw = runner.DeviceWorkload(w)
+    for flags in (0, binding.GSEARCH_FLAG_NO_BACKPOINTERS, binding.GSEARCH_FLAG_KEEP_PLANES,
+                  binding.GSEARCH_FLAG_NO_BIN_UNIT):
+        with runner.make_context(w, flags=flags) as ctx:
+            ctx.gsearch_set_knob("small", 1)
+            got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all"))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_small"
+            assert_same(got, ref, w, f"S={S} M={M} flags={flags}")
+            assert_curve(oracle_mod, ctx.gsearch_budget_curve().cpu().numpy(), w)
+            if flags & binding.GSEARCH_FLAG_KEEP_PLANES:
+                C, bp = ctx.gsearch_export_planes(want_bp=True)
+                C, bp = C.cpu().numpy(), bp.cpu().numpy()
+                for b in range(B):
+                    E = int(w.budget[b])
+                    one = oracle_mod.solve(w.T[b], w.O[b], w.R, w.r_index[b], E, want_planes=True)
+                    assert np.array_equal(bits(C[b, :, :E + 1, :]), bits(one["C"])), (S, M, b)
+                    assert np.array_equal(bp[b, :, :E + 1, :], one["bp"].astype(np.int32)), (S, M, b)
+
+
 @pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=4),
                                    dict(kernel=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
 @pytest.mark.parametrize("S", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 40, 41, 44, 45, 48])
