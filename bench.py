@@ -38,17 +38,20 @@ PROFILED = os.path.join(ROOT, "profiles", "traffic.json")
 def ops_per_relaxation(kernel: str, mode: str, S: int):
     """Vector-ALU instructions per relaxation that the kernel's algorithm needs.
 
-    min only: one add and half of a three-input minimum.  Flat argmin (push and generic
-    kernels): add, compare, two selects.  Two-level argmin (tile kernel): per chunk of
+    min only: one add and half of a three-input minimum.  Flat argmin over (sum, index) pairs
+    (push and one-launch kernels, tile kernel up to 48 strategies): an add and a minimum.  Two-level
+    argmin (tile kernel beyond, wide kernel): per chunk of
     eight candidates eight adds, four minimum instructions, one compare and two selects
     (15/8), plus the second look at one chunk per target state (8 adds, 8 compares,
-    8 selects = 24 per S relaxations).  None for k_dp_bound, which leaves sources out: how
+    8 selects = 24 per S relaxations).  Generic kernel: add, compare, two selects.  None for k_dp_bound, which leaves sources out: how
     many it scans depends on the tables and is not counted, so it has no ALU fraction.
     """
     if kernel == "k_dp_bound":
         return None
     if mode == "nobp":
         return 1.5
+    if kernel in ("k_dp_push", "k_dp_small") or (kernel == "k_dp_tile" and S <= 48):
+        return 2.0
     if kernel in ("k_dp_tile", "k_dp_wide"):
         return 15.0 / 8.0 + 24.0 / S
     return 4.0
@@ -250,7 +253,7 @@ def main():
             active = np.maximum(upper - np.minimum(skipped, upper), 0)
             executed = float(active.sum()) / float((rows * (w.L - 1)).sum())
             if not kernel.startswith(("k_dp_push", "k_dp_tile", "k_dp_wide", "k_dp_bound",
-                                      "k_dp_class")):
+                                      "k_dp_class", "k_dp_small")):
                 executed = 1.0
             n_class = int(out["n_class"].cpu()[0]) if "n_class" in out else None
             computed = float(active.sum()) / (w.L - 1)
