@@ -12,8 +12,8 @@
 // adds T and stores to row e' + O[l][sj].  Every C operand is read from HBM/L2 once and
 // reused S times from registers, so the kernel is bound by the vector ALU (one add and
 // the min/argmin bookkeeping per relaxation), or, with few strategies on large batches, by the
-// planes' way through HBM (outer search, 24 strategies, 2048 instances: 175 us per front with
-// backpointers, 3.9 TB/s; 209 us with a flat argmin of four instructions per relaxation).  The
+// planes' way through HBM (outer search, 24 strategies, 2048 instances: 160 us per front with
+// backpointers, 4.2 TB/s; 209 us with a flat argmin of four instructions per relaxation).  The
 // shifted stores stay coalesced because O[l][sj] is uniform across the wave.
 //
 // Rows e < O[l][sj] of the target cannot hold layer l under sj: they are set to +inf
@@ -153,21 +153,25 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_push(
     const float *__restrict__ Rt, const int32_t *__restrict__ ridx,
     const int32_t *__restrict__ budget, const int32_t *__restrict__ topsum,
     const int32_t *__restrict__ lowsum, int B, int L, int S,
-    int l, int pitch, int jsplit, int nblk) {
-  // Work item p = row_block * B + b (nblk of them): consecutive items belong to different
-  // instances, so every instance (and ragged budgets) spreads evenly over the chip.  The
-  // hardware deals consecutive workgroups round-robin to the eight XCDs, each with its own
-  // L2, and the jsplit workgroups that share one item read the same source rows: they are
-  // numbered so that they land on the same XCD and the rows are fetched into one L2 only,
+    int l, int pitch, int jsplit, int nblk, int row_blocks, bool by_instance) {
+  // Work items are (row block, instance) pairs, p of nblk.  The hardware deals consecutive
+  // workgroups round-robin to the eight XCDs, each with its own L2, and the jsplit workgroups that
+  // share one item read the same source rows: they are numbered so that they land on the same XCD
+  // and the rows are fetched into one L2 only,
   //   blockIdx.x = ((p / 8) * jsplit + js) * 8 + p % 8.
+  // by_instance: an XCD takes the row blocks of one instance one after the other, so that the
+  // parts of a cache line that two tiles store (the shifts are not aligned) meet in its L2; else
+  // consecutive items belong to different instances.
   const int q = blockIdx.x >> 3;
   const int js = q % jsplit;
   const int p = (q / jsplit) * 8 + (int)(blockIdx.x & 7);
   if (p >= nblk) return;
-  const int b = p % B;
+  const int b = by_instance ? (p >> 3) / row_blocks * 8 + (p & 7) : p % B;
+  const int rb = by_instance ? (p >> 3) % row_blocks : p / B;
+  if (b >= B) return; // (the batch is rounded up to a multiple of 8)
   const int wave = wave_uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int tile_start = ((p / B) * (int)(blockDim.x >> 6) + wave) * (kWave * RU);
+  const int tile_start = (rb * (int)(blockDim.x >> 6) + wave) * (kWave * RU);
   const int E = budget[b];
   if (tile_start > E) return;
   // this workgroup's slice of target strategies
@@ -2159,16 +2163,20 @@ static void launch_push_ru(const Shape &s, const Workspace &w, int l, const floa
                            float *dst, void *bp_l, int jsplit, int wpb, hipStream_t st) {
   const int rows = wpb * kWave * RU;
   const long long row_blocks = (s.M + 1 + rows - 1) / rows;
-  const long long nblk = row_blocks * s.B;
+  // Row blocks of an instance one after the other on one XCD: outer search (24 strategies, 2048
+  // instances) 5530 -> 5070 us with backpointers, 4460 -> 4120 without; a batch that is no multiple
+  // of 8 leaves XCDs one instance short, at most 1/32 from 256 on.
+  const bool by_instance = s.B % 8 == 0 || s.B >= 256;
+  const long long nblk = row_blocks * (by_instance ? (s.B + 7) / 8 * 8 : s.B);
   const dim3 grid((unsigned)((nblk + 7) / 8 * 8 * jsplit)), block(wpb * kWave);
   if (bp_l)
     hipLaunchKernelGGL((k_dp_push<SP, RU, true>), grid, block, 0, st, src, dst, (uint8_t *)bp_l,
                        w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.topsum, w.lowsum, s.B, s.L, s.S, l, s.pitch,
-                       jsplit, (int)nblk);
+                       jsplit, (int)nblk, (int)row_blocks, by_instance);
   else
     hipLaunchKernelGGL((k_dp_push<SP, RU, false>), grid, block, 0, st, src, dst,
                        (uint8_t *)nullptr, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.topsum, w.lowsum, s.B,
-                       s.L, s.S, l, s.pitch, jsplit, (int)nblk);
+                       s.L, s.S, l, s.pitch, jsplit, (int)nblk, (int)row_blocks, by_instance);
 }
 
 template <int SP>
@@ -2177,22 +2185,14 @@ static void launch_push(const Shape &s, const Workspace &w, int l, const float *
   int jsplit, wpb;
   push_launch_shape(s, jsplit, wpb);
   // Row groups per wave share a column's scalar loads, its T and O and the loop; they cost
-  // registers, so they need a batch that still fills the SIMDs.  Measured, 7 fronts, us at one /
-  // two / four groups: with backpointers S = 8 4096 tiles 50 / 46 / 55, 16384 124 / 107 / 105; S = 16
-  // 8192 137 / 135 / 142, 16384 233 / 215 / 215; S = 24 16384 339 / 348 / 356, 32768 893 / 814 / 730,
-  // outer search (2048 instances) 6160 / 5895 / 5620; S = 32 16384 545 / 541, 32768 1222 / 1159; S =
-  // 44 32768 1850 / 1953.  Min-only 5 % on the outer search.  The knob "row_groups" overrides.
+  // registers.  Measured, 7 fronts, us at one / two / four groups: S = 8 4096 tiles 52 / 50 / 56, 16384
+  // 122 / 108 / 110, 32768 209 / 179 / 182 (min-only 209 / 179 / 186); S = 16 8192 136 / 141 / 154, 16384
+  // 221 / 210 / 225 (min-only 214 / 200 / 196), 32768 450 / 473 / 473 (399 / 413 / 436); S = 24 16384
+  // 353 / 355 / 361, 32768 733 / 727 / 717 (582 / 621 / 608), outer search 5090 / 5340 / 5220; S = 32 32768
+  // 1053 / 1029 / 1014 (811 / 800 / 797); S = 44 1788 / 1925.  The knob "row_groups" overrides.
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.Bc * jsplit;
   int ru = s.tune.row_groups;
-  if (ru < 1) {
-    if (!bp_l) ru = tiles >= 4 * 8192 ? 4 : (tiles >= 2 * 8192 ? 2 : 1);
-    else if (SP <= 16) ru = tiles >= 24576 ? 4 : 2;
-    else if (SP <= 32) ru = tiles >= 24576 ? 4 : 1; // (two where there is no form of four)
-    else ru = 1;
-  }
-  if constexpr (SP <= 24) {
-    if (ru >= 4) return launch_push_ru<SP, 4>(s, w, l, src, dst, bp_l, jsplit, wpb, st);
-  }
+  if (ru < 1) ru = SP <= 16 && tiles >= (SP <= 8 ? 4096 : 12288) && (SP <= 8 || tiles < 24576) ? 2 : 1;
   if constexpr (SP <= 48) {
     if (ru >= 2) return launch_push_ru<SP, 2>(s, w, l, src, dst, bp_l, jsplit, wpb, st);
   }
@@ -2329,16 +2329,20 @@ bool fronts_shape_ok(const Shape &s) {
 //     292; and with one instance per XCD 44 to 162 strategies, 65 tiles, 174 / 204 .. 261 / 287, 24,
 //     94 tiles, 139 / 165 (the tiles of two fronts just about fill the XCD)
 // load - 3/4 of an even spread's load is what the uneven spread and the longer front cost; the
-// limits are where that eats the launches saved up.  Under eight layers, where the form's two small
+// limits are where that eats the launches saved up, with about half of the tiles having work; as
+// that share is not known here, batches that spread evenly keep the form up to 1.3 times the limit
+// and others take it up to 0.6 (96 strategies min-only, 4 instances, 229 tiles nearly all with work:
+// 802 / 1067 over 112 layers).  Under eight layers, where the form's two small
 // launches weigh more and either way is a matter of a few launches, batches that fill the XCDs
 // evenly take it.
 bool fronts_pay(const Shape &s, bool with_bp) {
   const long long tiles = (s.M + kWave) / kWave, q = (s.B + 7) / 8;
-  if (s.L < 8) return s.B % 8 == 0 || s.B >= 64;
+  const bool even = s.B % 8 == 0 || s.B >= 64;
+  if (s.L < 8) return even;
   if (!with_bp && q == 1 && tiles >= 64 && tiles <= 110) return false;
   const long long limit = with_bp ? (s.SP <= 48 ? 140 : s.SP <= 96 ? 92 : s.SP <= 128 ? 72 : 36)
                                   : (s.SP <= 96 ? 145 : s.SP <= 128 ? 120 : 75);
-  return 32 * q * tiles - 3 * s.B * tiles <= 32 * limit;
+  return 32 * q * tiles - 3 * s.B * tiles <= (even ? 42 : 19) * limit;
 }
 
 // Eight waves per tile, not four?  (Eight always with backpointers from 64 strategies up and from
