@@ -348,21 +348,27 @@ __global__ __launch_bounds__(NW *kWave) void k_dp_tile(
     if (compute) {
       const float *__restrict__ rc = rk + (size_t)j * SP;
       float m = GS_INF;
-      unsigned arg = 0;
-      if constexpr (WITH_BP && SP <= kFlatPairs) {
-        const pair_t p = scan_pairs<SP, SA>(c, rc, ix);
-        m = pair_sum(p);
-        arg = p.x;
-      } else {
-        int g = 0;
-        scan_chunks<SP, WITH_BP, SA>(m, g, c, rc);
-        if (WITH_BP) arg = chunk_argmin(tile + lane, rc, m, g);
-      }
+      int g = 0;
       const int eo = row + o;
-      if (row >= low && eo <= E) {
-        // the column's base stays a scalar 64-bit address, the lanes add a 32-bit row offset
-        (dstb + (size_t)j * pitch)[(uint32_t)eo] = m + t;
-        if (WITH_BP) (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)arg;
+      if constexpr (WITH_BP) {
+        unsigned arg;
+        if constexpr (SP <= kFlatPairs) {
+          const pair_t p = scan_pairs<SP, SA>(c, rc, ix);
+          m = pair_sum(p);
+          arg = p.x;
+        } else {
+          scan_chunks<SP, true, SA>(m, g, c, rc);
+          arg = chunk_argmin(tile + lane, rc, m, g);
+        }
+        if (row >= low && eo <= E) {
+          // the column's base stays a scalar 64-bit address, the lanes add a 32-bit row offset
+          (dstb + (size_t)j * pitch)[(uint32_t)eo] = m + t;
+          (bpb + (size_t)j * pitch)[(uint32_t)eo] = (uint8_t)arg;
+        }
+      } else {
+        scan_chunks<SP, false, SA>(m, g, c, rc);
+        float *__restrict__ dj = dstb + (size_t)j * pitch;
+        if (row >= low && eo <= E) dj[(uint32_t)eo] = m + t;
       }
     }
     if (tile_start < o + low) {
