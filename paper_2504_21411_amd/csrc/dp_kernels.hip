@@ -21,6 +21,7 @@
 // written exactly once per launch and nothing stale survives from an earlier solve.
 #include "gsearch_internal.h"
 #include "pair_min.h"
+#include "push_order.h"
 
 #include <type_traits>
 
@@ -153,22 +154,10 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_push(
     const float *__restrict__ Rt, const int32_t *__restrict__ ridx,
     const int32_t *__restrict__ budget, const int32_t *__restrict__ topsum,
     const int32_t *__restrict__ lowsum, int B, int L, int S,
-    int l, int pitch, int jsplit, int nblk, int row_blocks, bool by_instance) {
-  // Work items are (row block, instance) pairs, p of nblk.  The hardware deals consecutive
-  // workgroups round-robin to the eight XCDs, each with its own L2, and the jsplit workgroups that
-  // share one item read the same source rows: they are numbered so that they land on the same XCD
-  // and the rows are fetched into one L2 only,
-  //   blockIdx.x = ((p / 8) * jsplit + js) * 8 + p % 8.
-  // by_instance: an XCD takes the row blocks of one instance one after the other, so that the
-  // parts of a cache line that two tiles store (the shifts are not aligned) meet in its L2; else
-  // consecutive items belong to different instances.
-  const int q = blockIdx.x >> 3;
-  const int js = q % jsplit;
-  const int p = (q / jsplit) * 8 + (int)(blockIdx.x & 7);
-  if (p >= nblk) return;
-  const int b = by_instance ? (p >> 3) / row_blocks * 8 + (p & 7) : p % B;
-  const int rb = by_instance ? (p >> 3) % row_blocks : p / B;
-  if (b >= B) return; // (the batch is rounded up to a multiple of 8)
+    int l, int pitch, int jsplit, int row_blocks, int run) {
+  const PushItem it = push_item(blockIdx.x, jsplit, B, run);
+  const int b = it.b, rb = it.row_block, js = it.slice;
+  if (b >= B || rb >= row_blocks) return; // (rounding up)
   const int wave = wave_uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int tile_start = (rb * (int)(blockDim.x >> 6) + wave) * (kWave * RU);
@@ -2166,23 +2155,21 @@ static void launch_tile(const Shape &s, const Workspace &w, int l, const float *
 
 template <int SP, int RU>
 static void launch_push_ru(const Shape &s, const Workspace &w, int l, const float *src,
-                           float *dst, void *bp_l, int jsplit, int wpb, hipStream_t st) {
+                           float *dst, void *bp_l, int jsplit, int wpb, bool by_instance,
+                           hipStream_t st) {
   const int rows = wpb * kWave * RU;
   const long long row_blocks = (s.M + 1 + rows - 1) / rows;
-  // Row blocks of an instance one after the other on one XCD: outer search (24 strategies, 2048
-  // instances) 5530 -> 5070 us with backpointers, 4460 -> 4120 without; a batch that is no multiple
-  // of 8 leaves XCDs one instance short, at most 1/32 from 256 on.
-  const bool by_instance = s.B % 8 == 0 || s.B >= 256;
-  const long long nblk = row_blocks * (by_instance ? (s.B + 7) / 8 * 8 : s.B);
-  const dim3 grid((unsigned)((nblk + 7) / 8 * 8 * jsplit)), block(wpb * kWave);
+  int run = push_run(row_blocks, by_instance);
+  if (push_workgroups(row_blocks, s.B, jsplit, run) >= (1ll << 22)) run = 0; // (rounds up less)
+  const dim3 grid((unsigned)push_workgroups(row_blocks, s.B, jsplit, run)), block(wpb * kWave);
   if (bp_l)
     hipLaunchKernelGGL((k_dp_push<SP, RU, true>), grid, block, 0, st, src, dst, (uint8_t *)bp_l,
                        w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.topsum, w.lowsum, s.B, s.L, s.S, l, s.pitch,
-                       jsplit, (int)nblk, (int)row_blocks, by_instance);
+                       jsplit, (int)row_blocks, run);
   else
     hipLaunchKernelGGL((k_dp_push<SP, RU, false>), grid, block, 0, st, src, dst,
                        (uint8_t *)nullptr, w.Tq, w.Oq, w.Rt, w.ridx, w.budget, w.topsum, w.lowsum, s.B,
-                       s.L, s.S, l, s.pitch, jsplit, (int)nblk, (int)row_blocks, by_instance);
+                       s.L, s.S, l, s.pitch, jsplit, (int)row_blocks, run);
 }
 
 template <int SP>
@@ -2191,18 +2178,26 @@ static void launch_push(const Shape &s, const Workspace &w, int l, const float *
   int jsplit, wpb;
   push_launch_shape(s, jsplit, wpb);
   // Row groups per wave share a column's scalar loads, its T and O and the loop; they cost
-  // registers.  Measured, 7 fronts, us at one / two / four groups: S = 8 4096 tiles 52 / 50 / 56, 16384
-  // 122 / 108 / 110, 32768 209 / 179 / 182 (min-only 209 / 179 / 186); S = 16 8192 136 / 141 / 154, 16384
-  // 221 / 210 / 225 (min-only 214 / 200 / 196), 32768 450 / 473 / 473 (399 / 413 / 436); S = 24 16384
-  // 353 / 355 / 361, 32768 733 / 727 / 717 (582 / 621 / 608), outer search 5090 / 5340 / 5220; S = 32 32768
-  // 1053 / 1029 / 1014 (811 / 800 / 797); S = 44 1788 / 1925.  The knob "row_groups" overrides.
+  // registers.  Measured, 7 fronts, us at one / two groups, the order as push_by_instance says: S = 8
+  // 8064 tiles 85 / 76, 12600 tiles 100 / 85, 16384 143 / 131, 37888 262 / 220 (min-only 250 / 208); S = 16
+  // 11280 tiles 178 / 181, 16384 238 / 227, 16884 235 / 231 (min-only 244 / 229); beyond, by instance: S
+  // = 16 42210 652 / 681 (534 / 560), 65536 747 / 814, S = 24 24101 578 / 599 (500 / 523), 65536 1485 /
+  // 1542, S = 32 23475 799 / 822 (625 / 656); plain: S = 16 31300 471 / 461 (442 / 439), S = 24 31300 851 /
+  // 807 (683 / 654), 18760 421 / 416 (413 / 414), S = 32 15640 522 / 541 (461 / 479); S = 44 16380 968 /
+  // 1025.  The knob "row_groups" overrides (1 or 2).
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.Bc * jsplit;
+  const bool by_instance = push_by_instance(4ll * s.Bc * s.S * s.pitch, s.B);
   int ru = s.tune.row_groups;
-  if (ru < 1) ru = SP <= 16 && tiles >= (SP <= 8 ? 4096 : 12288) && (SP <= 8 || tiles < 24576) ? 2 : 1;
-  if constexpr (SP <= 48) {
-    if (ru >= 2) return launch_push_ru<SP, 2>(s, w, l, src, dst, bp_l, jsplit, wpb, st);
+  if (ru < 1) {
+    const bool two = SP <= 8    ? tiles >= 4096
+                     : SP <= 16 ? tiles >= 12288 && (tiles < 24576 || !by_instance)
+                                : SP <= 32 && tiles >= 24576 && !by_instance;
+    ru = two ? 2 : 1;
   }
-  launch_push_ru<SP, 1>(s, w, l, src, dst, bp_l, jsplit, wpb, st);
+  if constexpr (SP <= 48) {
+    if (ru >= 2) return launch_push_ru<SP, 2>(s, w, l, src, dst, bp_l, jsplit, wpb, by_instance, st);
+  }
+  launch_push_ru<SP, 1>(s, w, l, src, dst, bp_l, jsplit, wpb, by_instance, st);
 }
 
 bool class_path_applies(const Shape &s) {

@@ -1764,6 +1764,31 @@ def test_flat_argmin_of_pairs(gs, oracle_mod, S, knobs):
         assert np.array_equal(bp[b, :, :E + 1, :], one["bp"].astype(np.int32)), (S, b)
 
 
+@pytest.mark.parametrize("flags", [0, 0x4])
+@pytest.mark.parametrize("shape", [(259, 3, 8, 8100), (70, 3, 8, 31000), (8, 3, 8, 65535), (72, 3, 24, 1000),
+                                   (9, 4, 12, 700), (259, 4, 12, 300)], ids=lambda t: "B%dL%dS%dM%d" % t)
+def test_push_kernel_orders(gs, oracle_mod, shape, flags):
+    """Both numberings of the push kernel's workgroups (by instance from planes of 64 MB on) with one
+    and two row groups and slices of the targets: batches rounded up to a multiple of 8, row blocks
+    rounded up to an odd number, budgets that end anywhere."""
+    binding, runner = gs
+    B, L, S, M = shape
+    budget = np.array([(M, M // 8, M - 1, 5 * M // 8, M // 2, 255, M // 3, 256)[b % 8] for b in range(B)], np.int32)
+    w = random_tables("pushorder", B, L, S, M, K=2, seed=B + S, budget=budget, o_hi=M // L)
+    ref = oracle_batch(oracle_mod, w)
+    dw = runner.DeviceWorkload(w)
+    with runner.make_context(w, flags=flags) as ctx:
+        ctx.gsearch_set_knob("small", 0)
+        ctx.gsearch_set_knob("kernel", 1)
+        for jsplit, rows in ((0, 0), (1, 1), (3, 2)):
+            ctx.gsearch_set_knob("jsplit", jsplit)
+            ctx.gsearch_set_knob("row_groups", rows)
+            got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all"))
+            got["data_status"] = ctx.gsearch_data_status()
+            assert ctx.gsearch_forward_kernel() == "k_dp_push"
+            assert_same(got, ref, w, f"{shape} flags={flags} jsplit={jsplit} row_groups={rows}")
+
+
 @pytest.mark.parametrize("kernel,name", [(1, "k_dp_push"), (2, "k_dp_tile"), (3, "k_dp_wide")])
 @pytest.mark.parametrize("S", [49, 64, 80, 96, 100, 128])
 @pytest.mark.parametrize("flags", [0, 0x4])
