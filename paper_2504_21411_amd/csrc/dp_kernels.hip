@@ -2554,9 +2554,9 @@ static void launch_bound_as(const Shape &s, const Workspace &w, int l, const flo
 // solves of 12 layers, layer times of 1 to 10 and transition costs of up to 1 / 2 / 4 / 10 (how
 // far the bounds reach depends on that ratio; nothing is left out in the last one, which is also
 // what tables with a forbidden target per source take), new / old time:
-//   with backpointers  S = 29 to 32 against the tile kernel's flat argmin, 8 to 512 tiles 0.96 to 1.14 /
-//     1.03 to 1.35 / 1.28 to 1.47 / 1.28 to 1.39: not taken any more, but for the shortest searches (16
-//     tiles, or three an instance: 1.0 to 1.1 / 1.05 to 1.35), whose kernel is as it was; S = 44, 256 tiles 0.81 / 0.87 / 0.93 / 0.93 (520 tiles of the
+//   with backpointers  S = 29 to 32 against the tile kernel's flat argmin, 8 to 256 tiles 0.95 to 1.31 /
+//     1.00 to 1.33 / 1.25 to 1.51 / 1.25 to 1.39 (not taken); S = 34 8 to 252 tiles 0.77 to 0.97 / 0.83 to
+//     1.02 / 0.92 to 1.03 / 0.92 to 1.03; S = 44, 256 tiles 0.81 / 0.87 / 0.93 / 0.93 (520 tiles of the
 //     encoder-decoder batch lose: not taken); S = 64, 128 tiles 0.84 / 1.01 / 1.03 / 1.04, 512 tiles
 //     0.79 / 0.92 / 0.94 / 0.93, 1024 tiles 0.92 / 1.11 / 1.10 / 1.10 (not taken); S = 80, 256 tiles
 //     0.79 / 0.92 / 0.95 / 0.95, 512 tiles 0.91 / 1.12 / 1.12 / 1.11 (not taken: ten waves of eight
@@ -2577,8 +2577,7 @@ static void launch_bound_as(const Shape &s, const Workspace &w, int l, const flo
 static bool bound_pays(const Shape &s, bool with_bp) {
   const long long tiles = (long long)((s.M + kWave) / kWave) * s.Bc;
   switch (s.SP) {
-    case 32:
-      return s.S > 28 && tiles <= 256 && (!with_bp || tiles <= 16 || s.M < 3 * kWave);
+    case 32: return !with_bp && s.S > 28 && tiles <= 256;
     case 48: return tiles <= 256;
     case 64: return tiles <= 512;
     case 96: return s.S > 84 || tiles <= (with_bp ? 256 : 512) || (!with_bp && tiles >= 2048);
