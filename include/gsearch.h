@@ -238,8 +238,8 @@ int gsearch_instance_groups(gsearch_ctx *ctx);
  * general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
  * "jsplit" (waves per tile), "waves_per_block", "row_groups", "streams" (instance groups),
  * "fronts" (class kernel: layer fronts per launch, 2..64; 0 or 1: one launch per front; -1, the
- * default: 64 wherever that form can run and is the faster one, by the load of the fullest XCD; it
- * can run from three layers up, with no forced instance groups, on a GPU whose eight XCDs take
+ * default: 64 wherever that form can run and is the faster one, by the tiles with work that
+ * earlier solves of the context counted; it can run from three layers up, with no forced instance groups, on a GPU whose eight XCDs take
  * workgroups in turn; 2 or more ask for it wherever it can run),
  * "front_tiles" (that form: workgroups per instance and layer front, in eights; 0, the default: as
  * many as the fronts of earlier solves of the context had 64-row tiles with work, one per tile of

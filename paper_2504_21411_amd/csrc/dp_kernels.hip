@@ -2310,56 +2310,6 @@ bool fronts_shape_ok(const Shape &s) {
   return s.L >= 3 && (long long)(s.B + 7) * ((s.M + kWave) / kWave) < (1ll << 22);
 }
 
-// Whether several fronts per launch are the faster form.  Each XCD holds ceil(B / 8) instances, so
-// a front is as long as the `load` = ceil(B / 8) x tiles of the fullest XCD, while one launch per
-// front spreads the tiles evenly over all eight and costs two microseconds more per front at
-// least.  Measured (24 layers, 1 to 128 instances, 8 to 257 tiles, 24 to 162 strategies; whole
-// searches in us, one launch per front / several fronts per launch at the better of four and eight
-// waves):
-//   44 strategies, 47 tiles: 8 instances 165 / 140, 13 175 / 138, 24 173 / 146, 32 195 / 152, 64
-//     268 / 229, 128 396 / 410; 126 tiles: 8 169 / 133, 12 201 / 163, 24 266 / 221, 40 348 / 336, 48
-//     390 / 398; 251 tiles: 1 133 / 158, 5 181 / 159, 13 274 / 278; 7 tiles: 1 133 / 81, 13 139 / 91
-//   24: 63 tiles, 64 234 / 215, 128 340 / 386; 251 tiles, 4 162 / 131, 12 211 / 210, 24 287 / 295
-//   96: 65 tiles, 4 181 / 199, 8 197 / 196, 12 235 / 191, 32 353 / 329, 48 450 / 464, 128 925 / 1167;
-//     257 tiles, 4 265 / 320, 8 358 / 325, 12 471 / 598, 64 2012 / 2627
-//   128: 32 tiles, 8 215 / 181, 64 642 / 601, 100 926 / 945; 65 tiles, 24 488 / 464, 48 825 / 878
-//   162: 32 tiles, 8 253 / 219, 40 911 / 899, 64 1276 / 1406; 65 tiles, 4 304 / 373, 8 422 / 381
-//   min-only, 24: 63 tiles, 64 192 / 183, 100 252 / 260; 44: 126 tiles, 8 159 / 136, 48 328 / 332;
-//     96: 65 tiles, 12 208 / 181, 128 ... 471 / 424; 257 tiles, 8 313 / 262, 12 406 / 421; 128: 65
-//     tiles, 48 578 / 570, 60 709 / 734; 162: 65 tiles, 13 317 / 301, 40 663 / 650, 126 tiles, 4 267 /
-//     292; and with one instance per XCD 44 to 162 strategies, 65 tiles, 174 / 204 .. 261 / 287, 24,
-//     94 tiles, 139 / 165 (the tiles of two fronts just about fill the XCD)
-// load - 3/4 of an even spread's load is what the uneven spread and the longer front cost; the
-// limits are where that eats the launches saved up, with about half of the tiles having work; as
-// that share is not known here, batches that spread evenly keep the form up to 1.3 times the limit
-// and others take it up to 0.6 (96 strategies min-only, 4 instances, 229 tiles nearly all with work:
-// 802 / 1067 over 112 layers).  Under eight layers, where the form's two small
-// launches weigh more and either way is a matter of a few launches, batches that fill the XCDs
-// evenly take it.
-bool fronts_pay(const Shape &s, bool with_bp) {
-  const long long tiles = (s.M + kWave) / kWave, q = (s.B + 7) / 8;
-  const bool even = s.B % 8 == 0 || s.B >= 64;
-  if (s.L < 8) return even;
-  if (!with_bp && q == 1 && tiles >= 64 && tiles <= 110) return false;
-  const long long limit = with_bp ? (s.SP <= 48 ? 140 : s.SP <= 96 ? 92 : s.SP <= 128 ? 72 : 36)
-                                  : (s.SP <= 96 ? 145 : s.SP <= 128 ? 120 : 75);
-  return 32 * q * tiles - 3 * s.B * tiles <= (even ? 42 : 19) * limit;
-}
-
-// Eight waves per tile, not four?  (Eight always with backpointers from 64 strategies up and from
-// 128 up.)  Eight shorten a tile, but half as many tiles are on an XCD at a time (128): measured as
-// above, 44 strategies, four / eight: 47 tiles, 8 instances 153 / 140, 16 175 / 141, 24 188 / 146, 32
-// 152 / 177; 16 tiles, 48 142 / 124, 64 138 / 141, 128 179 / 229; 126 tiles, 8 262 / 133, 12 163 / 213;
-// min-only 47 tiles, 24 213 / 147, 32 183 / 167, 40 168 / 189; 24 strategies, one instance per XCD:
-// 157 tiles 219 / 128, 204 119 / 152, min-only 251 305 / 166; 96 min-only, 65 tiles, 24 302 / 222, 32
-// 278 / 291.
-static bool fronts_eight_waves(const Shape &s, bool with_bp, int used_tiles) {
-  const long long q = (s.B + 7) / 8, load = q * used_tiles;
-  if (with_bp) return s.SP >= 64 || load <= 112 || (q <= 3 && load <= 190);
-  if (s.SP >= 128 || (s.SP <= 32 && q == 1)) return true;
-  return load <= 160 || (q <= 4 && load <= 230);
-}
-
 template <int SP, int NW, int NC>
 static void launch_fronts_nc(const Shape &s, const Workspace &w, bool keep, bool with_bp,
                              size_t plane_elems_all, size_t bp_layer_bytes, int fronts, int ring,
@@ -2446,13 +2396,9 @@ static void launch_fronts_nw(const Shape &s, const Workspace &w, bool keep, bool
 
 template <int SP>
 static void launch_fronts(const Shape &s, const Workspace &w, bool keep, bool with_bp, size_t pe,
-                          size_t bpl, int fronts, int ring, int y0, unsigned *hint, int res,
-                          hipStream_t st) {
-  // waves per tile; y0: tiles with work that earlier solves found (0: not known)
-  const int tiles = (s.M + kWave) / kWave;
-  int waves = s.tune.jsplit;
-  if (waves < 1 || waves > 8)
-    waves = fronts_eight_waves(s, with_bp, y0 >= 1 && y0 < tiles ? y0 : tiles) ? 8 : 4;
+                          size_t bpl, int fronts, int waves, int ring, int y0, unsigned *hint,
+                          int res, hipStream_t st) {
+  if (s.tune.jsplit >= 1 && s.tune.jsplit <= 8) waves = s.tune.jsplit;
   if constexpr (SP > 128) {
     launch_fronts_nw<SP, 8>(s, w, keep, with_bp, pe, bpl, fronts, ring, y0, hint, res, st);
   } else {
@@ -2462,22 +2408,22 @@ static void launch_fronts(const Shape &s, const Workspace &w, bool keep, bool wi
 }
 
 // The forward pass of the class kernel with `fronts` layer fronts per launch (plus one small
-// launch for its dependency table).  plane_elems_all: floats per plane slot; bp_layer_bytes:
+// launch for its dependency table), `waves` waves per tile.  plane_elems_all: floats per plane slot; bp_layer_bytes:
 // backpointer bytes per layer.
 const char *launch_dp_class_fronts(const Shape &s, const Workspace &w, bool keep, bool with_bp,
                                    size_t plane_elems_all, size_t bp_layer_bytes, int fronts,
-                                   int ring, int y0, unsigned *hint, int resident_wgs,
+                                   int waves, int ring, int y0, unsigned *hint, int resident_wgs,
                                    hipStream_t st) {
   switch (s.SP) {
-    case 16: launch_fronts<16>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 24: launch_fronts<24>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 32: launch_fronts<32>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 48: launch_fronts<48>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 64: launch_fronts<64>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 96: launch_fronts<96>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 128: launch_fronts<128>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 192: launch_fronts<192>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
-    case 256: launch_fronts<256>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, ring, y0, hint, resident_wgs, st); break;
+    case 16: launch_fronts<16>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 24: launch_fronts<24>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 32: launch_fronts<32>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 48: launch_fronts<48>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 64: launch_fronts<64>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 96: launch_fronts<96>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 128: launch_fronts<128>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 192: launch_fronts<192>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
+    case 256: launch_fronts<256>(s, w, keep, with_bp, plane_elems_all, bp_layer_bytes, fronts, waves, ring, y0, hint, resident_wgs, st); break;
     default: break; // class_path_applies() admits no other pitch
   }
   return "k_dp_class_fronts";

@@ -9,6 +9,7 @@
 #include <vector>
 #include <new>
 
+#include "class_form.h"
 #include "gsearch_internal.h"
 
 namespace {
@@ -199,6 +200,10 @@ struct gsearch_ctx {
   // it can reach), and the next call reads whatever has arrived, without waiting.  A count
   // that is out of date costs time, never results (see k_dp_class_fronts_plain).
   unsigned *front_hint = nullptr;
+  // The same as a share: the count last read, and the tiles of the budget of the solve taken to
+  // have written it (the last one of that form before the count was seen to change).
+  unsigned front_seen = 0;
+  int front_seen_tiles = 0, front_last_tiles = 0;
   int resident_wgs = 0; // workgroups of 512 threads the GPU surely holds at once
   gs::Tuning tune;      // launch overrides (from the environment at create, gsearch_set_knob)
   gs::LdsGrants grants; // LDS sizes already asked for, per kernel
@@ -267,13 +272,47 @@ __global__ void k_set_word(uint32_t *__restrict__ p, uint32_t v) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *p = v;
 }
 
-// Layer fronts per launch of the class kernel (0: one launch per front).  The several-fronts
-// form needs the eight XCDs to take workgroups in turn; a knob of 2 or more asks for it wherever
-// it can run.
-int fronts_per_launch(const gsearch_ctx *ctx, const gs::Shape &s, bool with_bp) {
-  if (!ctx->fronts_ok || !gs::fronts_shape_ok(s) || ctx->groups > 1) return 0;
-  if (ctx->tune.fronts < 0) return gs::fronts_pay(s, with_bp) ? 64 : 0;
-  return ctx->tune.fronts >= 2 ? ctx->tune.fronts : 0;
+// How a solve runs the class kernel.
+struct FrontsPlan {
+  int fronts; // layer fronts per launch (0: one launch per front)
+  int waves;  // per tile
+  int y0;     // workgroups per instance and front (0: one per tile of the budget)
+};
+
+// The several-fronts form needs the eight XCDs to take workgroups in turn; a knob of 2 or more asks
+// for it wherever it can run.  By itself a solve takes the form that is the fastest for the tiles with
+// work that earlier solves of the context counted, as a share of all (another shape may have come
+// between); a solve with one launch per front counts nothing, so the share stays until then.  Under
+// eight layers, where either way is a matter of a few launches, batches that spread evenly over the
+// XCDs take the several-fronts form.
+FrontsPlan plan_fronts(gsearch_ctx *ctx, const gs::Shape &s, bool with_bp) {
+  if (!ctx->fronts_ok || !gs::fronts_shape_ok(s) || ctx->groups > 1) return {0, 0, 0};
+  const int tiles = (s.M + gs::kWave) / gs::kWave;
+  const bool whole = (ctx->cfg.flags & GSEARCH_FLAG_KEEP_PLANES) != 0; // no row is left out
+  // workgroups: what the fronts of earlier solves needed and a sixteenth more (four at least); all
+  // tiles while nothing is known, after a solve that did not fit, and where no row is left out
+  int y0 = 0, used = whole ? tiles : 0;
+  if (ctx->front_hint && !whole) {
+    const unsigned seen = *static_cast<volatile unsigned *>(ctx->front_hint);
+    if (seen >= 1u && seen < (1u << 22)) {
+      const int count = (int)seen;
+      y0 = count + (count / 16 > 4 ? count / 16 : 4);
+      if (seen != ctx->front_seen) {
+        ctx->front_seen = seen;
+        ctx->front_seen_tiles = ctx->front_last_tiles;
+      }
+      long long share = count;
+      if (ctx->front_seen_tiles > 0) share = share * tiles / ctx->front_seen_tiles;
+      share += share / 16 > 4 ? share / 16 : 4;
+      used = (int)(share < tiles ? share : tiles);
+    }
+  }
+  const gs::ClassForm form = used ? gs::class_form(s.B, s.L, s.SP, with_bp, (float)used)
+                                  : gs::class_form_unknown(s.B, s.L, s.SP, with_bp, tiles);
+  int fronts = ctx->tune.fronts;
+  if (fronts < 0) fronts = (s.L < 8 ? s.B % 8 == 0 || s.B >= 64 : form.pays) ? 64 : 0;
+  if (fronts < 2) return {0, 0, 0};
+  return {fronts, form.waves, y0};
 }
 
 // The solve behind gsearch_solve_batch and gsearch_solve_batch_noalloc.
@@ -374,6 +413,7 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
     bp_layer_bytes = (size_t)s.B * bp_inst_bytes;
   }
   ctx->ws = w;
+  const FrontsPlan plan = use_classes ? plan_fronts(ctx, s, with_bp) : FrontsPlan{0, 0, 0};
   int cur = 0;
   ctx->timed = false;
   const bool timing = ctx->profiling && s.L > 1;
@@ -384,24 +424,16 @@ int solve_impl(gsearch_ctx *ctx, const gsearch_problem *p, const gsearch_result 
     gs::launch_dp_small(s, w, keep, (c.flags & GSEARCH_FLAG_KEEP_PLANES) != 0, cur, st);
     ctx->forward_kernel = "k_dp_small";
     ctx->groups_used = 1;
-  } else if (use_classes && fronts_per_launch(ctx, s, with_bp) > 0) {
+  } else if (plan.fronts > 0) {
     // several layer fronts per launch, the instances bound to XCDs (see k_dp_class_fronts)
     if (keep) gs::launch_class_zero(s, w.planes, st);
     if (timing && hipEventRecord(ctx->ev_begin, st) != hipSuccess) return GSEARCH_ERR_HIP;
     // (a power of two; not used when the planes are kept)
     const int ring = y.nplanes < kFrontRing ? 2 : kFrontRing;
-    // workgroups per instance and front: what the fronts of earlier solves needed and a
-    // sixteenth more (four at least); all tiles while nothing is known, after a solve that
-    // did not fit, and where no row is left out
-    int y0 = 0;
-    if (ctx->front_hint && !(c.flags & GSEARCH_FLAG_KEEP_PLANES)) {
-      const unsigned seen = *static_cast<volatile unsigned *>(ctx->front_hint);
-      if (seen >= 1u && seen < (1u << 22))
-        y0 = (int)seen + ((int)seen / 16 > 4 ? (int)seen / 16 : 4);
-    }
     ctx->forward_kernel = gs::launch_dp_class_fronts(s, w, keep, with_bp, pe, bp_layer_bytes,
-                                                     fronts_per_launch(ctx, s, with_bp), ring, y0,
+                                                     plan.fronts, plan.waves, ring, plan.y0,
                                                      ctx->front_hint, ctx->resident_wgs, st);
+    ctx->front_last_tiles = (s.M + gs::kWave) / gs::kWave;
     ctx->groups_used = 1;
     cur = keep ? s.L - 1 : ((s.L - 1) & (ring - 1));
   } else {

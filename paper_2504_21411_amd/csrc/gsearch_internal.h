@@ -133,7 +133,8 @@ const char *launch_dp_class(const Shape &s, const Workspace &w, int l, const flo
                             float *dst, void *bp_l, hipStream_t st);
 void launch_class_zero(const Shape &s, float *q0, hipStream_t st);
 // The forward pass of the class kernel with `fronts` layer fronts per launch, the tiles of a
-// launch waiting for each other through flags (3 layers or more; any batch, see fronts_pay).
+// launch waiting for each other through flags (3 layers or more; any batch).  waves: per tile,
+// 4 or 8 (see class_form.h).
 // Unless the planes are kept, Q[l] goes to plane slot l % ring (ring = 2 or 4 slots are there).
 // y0: workgroups per instance and front (0: one per tile of the budget); a solve in which a
 // front has more tiles with work than that is redone by a slow launch behind the fast ones.
@@ -141,10 +142,9 @@ void launch_class_zero(const Shape &s, float *q0, hipStream_t st);
 // any front.  resident_wgs: workgroups of 512 threads the GPU surely holds at once.
 const char *launch_dp_class_fronts(const Shape &s, const Workspace &w, bool keep, bool with_bp,
                                    size_t plane_elems_all, size_t bp_layer_bytes, int fronts,
-                                   int ring, int y0, unsigned *hint, int resident_wgs,
+                                   int waves, int ring, int y0, unsigned *hint, int resident_wgs,
                                    hipStream_t st);
-bool fronts_shape_ok(const Shape &s);              // that form can take this shape
-bool fronts_pay(const Shape &s, bool with_bp);     // and it is the faster one
+bool fronts_shape_ok(const Shape &s); // that form can take this shape
 // out[i] = id of the XCD that workgroup i of a grid of kXccProbeGrid workgroups ran on
 constexpr int kXccProbeGrid = 512;
 void launch_xcc_probe(unsigned *out, hipStream_t st);

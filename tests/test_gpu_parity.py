@@ -732,20 +732,58 @@ def test_several_fronts_per_launch_for_any_batch(gs, oracle_mod, shape, mode, js
             assert_same(got, ref, w, f"{mode} jsplit={jsplit} rep {rep}")
 
 
-def test_the_form_of_the_class_kernel_follows_the_load_of_an_xcd(gs):
-    """Which searches take several fronts per launch by themselves: not those whose uneven spread
-    over the XCDs, or whose long fronts, cost more than the launches saved."""
+@pytest.mark.parametrize("B,L,S,tiles,flags,work,first,later", [
+    (8, 3, 24, 4, 0, 1.0, True, True), (9, 7, 24, 4, 0, 1.0, False, False), (9, 8, 24, 4, 0, 1.0, True, True),
+    (1, 24, 44, 47, 0, 1.0, True, False), (1, 24, 44, 47, 0, 0.25, True, True),
+    (8, 12, 24, 200, 4, 1.0, True, False), (64, 12, 24, 40, 4, 1.0, True, True),
+    (1, 8, 128, 126, 0, 1.0, False, False), (8, 8, 128, 126, 0, 1.0, True, True)])
+def test_the_form_of_the_class_kernel_follows_the_tiles_with_work(gs, oracle_mod, B, L, S, tiles, flags,
+                                                                 work, first, later):
+    """Which searches take several fronts per launch by themselves: by the costs of the forms, at first
+    without knowing how many tiles have work, then by what the first solves counted; under eight layers
+    batches that spread evenly.  Results are the same either way."""
     _, runner = gs
     import torch
-    for B, L, S, M, flags, kernel in ((8, 3, 24, 200, 0, "k_dp_class_fronts"),
-                                      (9, 7, 24, 200, 0, "k_dp_class"), (9, 8, 24, 200, 0, "k_dp_class_fronts"),
-                                      (1, 8, 128, 8000, 0, "k_dp_class"), (8, 8, 128, 8000, 0, "k_dp_class_fronts"),
-                                      (8, 8, 24, 5000, 0, "k_dp_class_fronts"), (8, 8, 24, 5000, 4, "k_dp_class")):
-        w, r_class = workloads.class_tables("form", B, L, S, M, [4] * (S // 4), K=1, seed=B)
+    M = 64 * tiles - 1
+    w, r_class = workloads.class_tables("form", B, L, S, M, [4] * (S // 4), K=1, seed=B)
+    w.O[:] = 1 + int((1.0 - work) * M / L) + np.arange(S, dtype=np.int32) % 3
+    w.budget[:] = M
+    ref = oracle_batch(oracle_mod, w)
+    dw = runner.DeviceWorkload(w)
+    rc = torch.from_numpy(r_class).to(dw.device)
+    with runner.make_context(w, flags=flags) as ctx:
+        for rep in range(3):
+            got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all", r_class=rc))
+            got["data_status"] = ctx.gsearch_data_status()
+            several = later if rep else first
+            assert ctx.gsearch_forward_kernel() == ("k_dp_class_fronts" if several else "k_dp_class"), rep
+            assert_same(got, ref, w, f"{B} {L} {S} {tiles} flags={flags} rep {rep}")
+
+
+def test_the_form_of_one_shape_is_not_another_shapes_count(gs):
+    """Two shapes in turn in one context: the tiles with work that one counted reach the other as a
+    share of its tiles, not as a number (44 strategies, 47 tiles all with work: one launch per front;
+    9 tiles: several fronts)."""
+    _, runner = gs
+    import torch
+    L, S = 24, 44
+    made = []
+    for tiles in (47, 9):
+        M = 64 * tiles - 1
+        w, r_class = workloads.class_tables("share", 1, L, S, M, [4] * 11, K=1, seed=tiles)
+        w.O[:] = 1 + np.arange(S, dtype=np.int32) % 3
+        w.budget[:] = M
         dw = runner.DeviceWorkload(w)
-        with runner.make_context(w, flags=flags) as ctx:
-            runner.run_step(ctx, dw, backtrace=None, r_class=torch.from_numpy(r_class).to(dw.device))
-            assert ctx.gsearch_forward_kernel() == kernel, (B, L, S, M, flags)
+        made.append((dw, torch.from_numpy(r_class).to(dw.device)))
+    with runner.make_context(made[0][0].w) as ctx:
+        def form(i):
+            runner.run_step(ctx, made[i][0], backtrace=None, r_class=made[i][1])
+            torch.cuda.synchronize()
+            return ctx.gsearch_forward_kernel()
+        assert form(1) == "k_dp_class_fronts"               # nothing known; 9 tiles of 9 counted
+        assert form(0) == "k_dp_class"                      # ... so all 47 are expected to have work
+        assert form(1) == "k_dp_class_fronts"
+        assert form(0) == "k_dp_class"
 
 
 def test_several_fronts_per_launch_on_other_streams_and_in_a_graph(gs, oracle_mod):
