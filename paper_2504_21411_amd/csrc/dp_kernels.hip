@@ -1834,10 +1834,10 @@ __global__ __launch_bounds__(kRowsPerBlock) void k_dp_generic(
 // Bound by the vector ALU of the one compute unit and, with many targets a thread, by LDS: a column
 // read by all lanes costs a wave 2 cycles a value like any other, so while a thread has few targets
 // their columns stay in its registers and are read again only when the layer's transition matrix
-// is another (12 strategies, 256 bins, 23 fronts: 36.6 -> 34.2 us).  Measured, 23 fronts, before (flat
-// compare and two selects, every row, sources padded to a multiple of eight) / now: 12 strategies
-// 256 bins 63 / 34 us, 768 143 / 79; 8 strategies 512 bins 66 / 33; 16 / 256 80 / 48; 24 / 128 98 / 50,
-// 24 / 384 224 / 108; 32 / 64 188 / 48.
+// is another (12 strategies, 256 bins, 23 fronts: 36.6 -> 34.1 us).  Measured, 23 fronts, us, this
+// kernel before (flat compare and two selects, every row, sources padded to a multiple of eight) / now:
+// 12 strategies 256 bins 62 / 34, 768 139 / 80 (the rule ran the tile kernel: 96); 8 strategies 512 bins
+// 66 / 36; 16 / 256 86 / 49; 24 / 128 99 / 50; 32 / 64 122 / 49.
 // ---------------------------------------------------------------------------------------
 template <int SQ, bool WITH_BP>
 static __device__ __forceinline__ void small_scan(const float (&c)[SQ], const float (&r)[SQ],
@@ -2014,17 +2014,17 @@ bool small_path_applies(const Shape &s, bool with_bp) {
   // One workgroup per instance means one compute unit per instance, so the one-launch kernel
   // wins only while a layer front is short for one.  Measured per layer (24 layers, 1 and 64
   // instances, S = 4..32, M = 64..1000), in microseconds, within a tenth or so:
-  //   one launch  0.5 + 0.00078 tiles S (S + 8) with backpointers, 0.00066 without
+  //   one launch  0.5 + 0.00078 tiles S (S + 8) with backpointers, 0.00069 without
   //   tile kernel 1.9 + 0.115 S per launch
-  // e.g. 23 fronts, us, tile / one launch: S = 8, 1000 bins 70 / 51; S = 12, 768 83 / 79, 1000 83 / 91
-  // (min-only 82 / 78); S = 16, 512 89 / 76; S = 20, 384 103 / 87, 512 104 / 102; S = 24, 256 101 / 77, 384
-  // 106 / 108 (min-only 105 / 94); S = 32, 256 138 / 118.  The knob "small" = 0 / 1 (tuning) switches the
-  // path off / on wherever it fits.
+  // e.g. 23 fronts, us, tile / one launch: S = 8, 1000 bins 71 / 54 (min-only 71 / 48); S = 12, 768 84 / 80
+  // (83 / 69), 1000 84 / 88 (83 / 72); S = 16, 512 90 / 77 (89 / 67); S = 20, 384 103 / 88, 512 106 / 103
+  // (103 / 89); S = 24, 256 103 / 78, 384 106 / 109 (107 / 94), 500 109 / 132 (108 / 112); S = 32, 256 126 /
+  // 120 (121 / 99).  The knob "small" = 0 / 1 (tuning) switches the path off / on wherever it fits.
   const int forced = s.tune.small;
   if (forced == 0 || forced == 1) return forced == 1;
   const double rounds = (s.B + 255) / 256; // (256 compute units)
   const double front = (double)((s.M + kWave) / kWave) * s.S * (s.S + 8);
-  return rounds * (0.5 + (with_bp ? 0.00078 : 0.00066) * front) <= 1.9 + 0.115 * s.S;
+  return rounds * (0.5 + (with_bp ? 0.00078 : 0.00069) * front) <= 1.9 + 0.115 * s.S;
 }
 
 // More than 64 KB of dynamic LDS per workgroup has to be asked for, per kernel: the context's

@@ -1771,6 +1771,18 @@ def test_one_launch_kernel_forms(gs, oracle_mod, S, M):
                     assert np.array_equal(bp[b, :, :E + 1, :], one["bp"].astype(np.int32)), (S, M, b)
 
 
+@pytest.mark.parametrize("S,M,flags,kernel", [(24, 500, 4, "k_dp_tile"), (24, 384, 4, "k_dp_small"),
+                                              (12, 1000, 4, "k_dp_small"), (24, 384, 0, "k_dp_tile"),
+                                              (24, 256, 0, "k_dp_small"), (12, 1000, 0, "k_dp_tile")])
+def test_one_launch_kernel_is_taken_where_it_is_the_faster(gs, S, M, flags, kernel):
+    """Single searches at both sides of the rule's line (figures beside it)."""
+    _, runner = gs
+    w = random_tables("smallrule", 1, 24, S, M, seed=S)
+    with runner.make_context(w, flags=flags) as ctx:
+        runner.run_step(ctx, runner.DeviceWorkload(w), backtrace=None)
+        assert ctx.gsearch_forward_kernel() == kernel
+
+
 @pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=4),
                                    dict(kernel=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
 @pytest.mark.parametrize("S", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 40, 41, 44, 45, 48])
