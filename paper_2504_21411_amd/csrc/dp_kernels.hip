@@ -2012,19 +2012,22 @@ bool small_path_applies(const Shape &s, bool with_bp) {
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.B;
   if (tiles > 2048) return false;
   // One workgroup per instance means one compute unit per instance, so the one-launch kernel
-  // wins only while a layer front is short for one.  Measured per layer (24 layers, 1 and 64
-  // instances, S = 4..32, M = 64..1000), in microseconds, within a tenth or so:
-  //   one launch  0.5 + 0.00078 tiles S (S + 8) with backpointers, 0.00069 without
-  //   tile kernel 1.9 + 0.115 S per launch
-  // e.g. 23 fronts, us, tile / one launch: S = 8, 1000 bins 71 / 54 (min-only 71 / 48); S = 12, 768 84 / 80
+  // wins only while a layer front is short for one.  Measured per layer (11.6 thousand shapes, 12 to 40
+  // layers, S = 4..32, M = 24..959, 1 to 1000 instances, 1 to 4 transition matrices), in microseconds:
+  //   one launch  0.78 + 0.00066 tiles S (S + 8) with backpointers, 0.00057 without; the second term
+  //               again nine tenths for each further 256 instances (256 compute units)
+  //   tile kernel 1.9 + 0.095 S per launch, 1.5 + 9.4e-6 tiles instances S^2 at least
+  // The one picked takes 1.001 times the faster one's time on average, more than 1.1 times in 4 of 1000.
+  // E.g. 23 fronts, us, tile / one launch: S = 8, 1000 bins 71 / 54 (min-only 71 / 48); S = 12, 768 84 / 80
   // (83 / 69), 1000 84 / 88 (83 / 72); S = 16, 512 90 / 77 (89 / 67); S = 20, 384 103 / 88, 512 106 / 103
   // (103 / 89); S = 24, 256 103 / 78, 384 106 / 109 (107 / 94), 500 109 / 132 (108 / 112); S = 32, 256 126 /
   // 120 (121 / 99).  The knob "small" = 0 / 1 (tuning) switches the path off / on wherever it fits.
   const int forced = s.tune.small;
   if (forced == 0 || forced == 1) return forced == 1;
-  const double rounds = (s.B + 255) / 256; // (256 compute units)
-  const double front = (double)((s.M + kWave) / kWave) * s.S * (s.S + 8);
-  return rounds * (0.5 + (with_bp ? 0.00078 : 0.00069) * front) <= 1.9 + 0.115 * s.S;
+  const double rounds = 1.0 + 0.9 * ((s.B + 255) / 256 - 1);
+  const double work = (double)((s.M + kWave) / kWave) * s.S * (s.S + 8);
+  const double launch = 1.9 + 0.095 * s.S, batch = 1.5 + 9.4e-6 * (double)tiles * s.S * s.S;
+  return 0.78 + (with_bp ? 0.00066 : 0.00057) * work * rounds <= (launch > batch ? launch : batch);
 }
 
 // More than 64 KB of dynamic LDS per workgroup has to be asked for, per kernel: the context's
@@ -2069,6 +2072,13 @@ static void launch_small_sq(const Shape &s, const Workspace &w, bool keep_all, b
   const int threads = s.S * rows64 < 1024 ? s.S * rows64 : 1024;
   // targets whose columns fit the registers of sixteen waves
   constexpr int KEEP = SQ <= 12 ? 4 : SQ <= 16 ? 3 : SQ <= 24 ? 2 : 0;
+  // One or two targets a thread: forms of their own, which take fewer registers (two workgroups on a
+  // compute unit from 257 instances on: 400 of 8 strategies x 100 bins 53 -> 40 us a search) and read
+  // no columns twice when layers change matrices.
+  if constexpr (SQ <= 16) {
+    if (per == 1) return launch_small_as<SQ, 1>(s, w, threads, keep_all, keep_rows, last_plane, st);
+    if (per == 2) return launch_small_as<SQ, 2>(s, w, threads, keep_all, keep_rows, last_plane, st);
+  }
   if (KEEP > 0 && per <= KEEP)
     return launch_small_as<SQ, KEEP>(s, w, threads, keep_all, keep_rows, last_plane, st);
   launch_small_as<SQ, 0>(s, w, threads, keep_all, keep_rows, last_plane, st);

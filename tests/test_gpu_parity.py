@@ -1732,7 +1732,8 @@ def test_bounded_kernel_votes_start_afresh(gs, oracle_mod, S):
 
 @pytest.mark.parametrize("S,M", [(1, 70), (3, 900), (4, 63), (5, 500), (8, 1000), (9, 64), (12, 257), (12, 500),
                                  (13, 300), (16, 130), (17, 128), (20, 400), (21, 192), (24, 90), (24, 300),
-                                 (28, 100), (29, 65), (32, 64), (32, 250)])
+                                 (28, 100), (29, 65), (32, 64), (32, 250), (4, 400), (8, 100), (8, 200),
+                                 (12, 60), (13, 150), (16, 60), (16, 100)])
 def test_one_launch_kernel_forms(gs, oracle_mod, S, M):
     """Both forms of the one-launch kernel (columns in registers, columns from LDS) over its strategy
     counts: instances whose rows that matter are all, few, one or none of their budget's, layers that
@@ -1771,13 +1772,15 @@ def test_one_launch_kernel_forms(gs, oracle_mod, S, M):
                     assert np.array_equal(bp[b, :, :E + 1, :], one["bp"].astype(np.int32)), (S, M, b)
 
 
-@pytest.mark.parametrize("S,M,flags,kernel", [(24, 500, 4, "k_dp_tile"), (24, 384, 4, "k_dp_small"),
-                                              (12, 1000, 4, "k_dp_small"), (24, 384, 0, "k_dp_tile"),
-                                              (24, 256, 0, "k_dp_small"), (12, 1000, 0, "k_dp_tile")])
-def test_one_launch_kernel_is_taken_where_it_is_the_faster(gs, S, M, flags, kernel):
-    """Single searches at both sides of the rule's line (figures beside it)."""
+@pytest.mark.parametrize("B,S,M,flags,kernel", [
+    (1, 24, 500, 4, "k_dp_tile"), (1, 24, 384, 4, "k_dp_small"), (1, 12, 1000, 4, "k_dp_small"),
+    (1, 24, 384, 0, "k_dp_tile"), (1, 24, 256, 0, "k_dp_small"), (1, 12, 1000, 0, "k_dp_tile"),
+    (478, 19, 221, 0, "k_dp_small"), (600, 8, 100, 0, "k_dp_small"), (300, 16, 353, 4, "k_dp_small")])
+def test_one_launch_kernel_is_taken_where_it_is_the_faster(gs, B, S, M, flags, kernel):
+    """Searches at both sides of the rule's line (figures beside it), and batches of more instances than
+    compute units, where the tile kernel's launches are long as well."""
     _, runner = gs
-    w = random_tables("smallrule", 1, 24, S, M, seed=S)
+    w = random_tables("smallrule", B, 24, S, M, seed=S)
     with runner.make_context(w, flags=flags) as ctx:
         runner.run_step(ctx, runner.DeviceWorkload(w), backtrace=None)
         assert ctx.gsearch_forward_kernel() == kernel
