@@ -70,12 +70,18 @@ def class_ops_per_row(S: int, nc: int, maxlen: int, nobp: bool) -> float:
     return ops + 15.0 / 8.0 * nc * nc + nc * (24.0 + 3.0 * maxlen)
 
 
-def load_profiled():
+def load_profiled(path=PROFILED):
+    """The profile, with the entries alone that were taken of the kernels as they are built now:
+    bytes of another version of a kernel say nothing about a launch of this one."""
+    from paper_2504_21411_amd.profile_summary import kernel_sources_digest
     try:
-        with open(PROFILED) as f:
-            return json.load(f)
-    except (OSError, ValueError):
+        with open(path) as f:
+            d = json.load(f)
+        now = kernel_sources_digest()
+        entries = {k: e for k, e in d["entries"].items() if e.get("sources", d.get("sources")) == now}
+    except (OSError, ValueError, KeyError):
         return {}
+    return dict(d, entries=entries, commit=d.get("commit") if entries else None)
 
 
 def profile_of(kernel, entry):

@@ -25,17 +25,35 @@ averaged per dispatch of the forward kernel (the gs::k_dp_* kernel with the larg
 of the run).  HBM bytes = FETCH_SIZE and WRITE_SIZE scaled by what the same counters read for a
 plain copy of known size; LDS bytes = the three LDS bandwidth counters scaled by what they read
 for LDS kernels of known size (four-byte loads, stores and atomics; the sixteen-byte load
-factor is recorded beside them).  Only reads the databases and writes the two files: no
-measurement happens here.
+factor is recorded beside them).  The document names the kernels it was taken of by a digest of
+their sources ("sources"), and bench.py uses no entry of other sources.  Only reads the databases
+and writes the two files: no measurement happens here.
 """
 from __future__ import annotations
 
 import argparse
 import glob
+import hashlib
 import json
 import os
+import re
 import sqlite3
 import time
+
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
+
+
+def kernel_sources_digest(folder=CSRC):
+    """Digest of the kernels' sources and of what launches them, without comments and layout."""
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(folder)):
+        if not name.endswith((".hip", ".h", ".cpp")):
+            continue
+        with open(os.path.join(folder, name)) as f:
+            code = re.sub(r"/\*.*?\*/|//[^\n]*", " ", f.read(), flags=re.S)
+        h.update((name + "\n" + " ".join(code.split()) + "\n").encode())
+    return h.hexdigest()[:16]
 
 
 def _dbs(folder):
@@ -258,7 +276,7 @@ def main():
                     f"write {e.get('write_bytes', float('nan')) / 1e6:.2f}), "
                     f"LDS {e.get('lds_bytes', float('nan')) / 1e6:.2f} MB per launch")
     doc = {"commit": args.commit, "written": time.strftime("%Y-%m-%d"), "device": "MI355X (gfx950)",
-           "calibration": calib, "entries": entries}
+           "sources": kernel_sources_digest(), "calibration": calib, "entries": entries}
     with open(args.out, "w") as f:
         json.dump(doc, f, indent=1, sort_keys=True)
         f.write("\n")

@@ -31,6 +31,32 @@ def test_no_alu_fraction_without_a_count_and_no_counters_of_another_kernel():
     assert bench.profile_of("k_dp_bound", entry) == {} and bench.profile_of("k_dp_bound", None) == {}
 
 
+def test_counters_of_other_sources_are_not_used(tmp_path):
+    """A kernel that was rewritten keeps its name; its old bytes and durations are not its own."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2504_21411_amd.profile_summary import kernel_sources_digest
+    src = tmp_path / "csrc"
+    src.mkdir()
+    digests = []
+    for text in ("int a; // one\n", "int  a; /* two\n */\n", "int b;\n"):
+        (src / "k.hip").write_text(text)
+        digests.append(kernel_sources_digest(str(src)))
+    assert digests[0] == digests[1] != digests[2]          # comments and layout do not count
+    path = tmp_path / "traffic.json"
+    for sources, own, kept in ((None, None, []), (digests[2], None, []), (kernel_sources_digest(), None, ["a", "b"]),
+                               (digests[2], kernel_sources_digest(), ["b"])):
+        d = {"commit": "c", "entries": {"a": {"kernel": "k"}, "b": {"kernel": "k"}}}
+        if sources:
+            d["sources"] = sources
+        if own:
+            d["entries"]["b"]["sources"] = own
+        path.write_text(json.dumps(d))
+        got = bench.load_profiled(str(path))
+        assert sorted(got["entries"]) == kept and got["commit"] == ("c" if kept else None)
+    assert bench.load_profiled(str(tmp_path / "none.json")) == {}
+
+
 @pytest.mark.gpu
 def test_bench_reports_no_alu_fraction_for_the_bounded_kernel():
     p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--mode", "bp-general",
