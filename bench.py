@@ -90,6 +90,19 @@ def profile_of(kernel, entry):
     return dict(entry) if name.split("<")[0] == kernel else {}
 
 
+def per_front(kernel, prof, L):
+    """(figures of the profile per layer front, layer fronts per launch): a launch of the one-launch
+    kernel covers all L - 1 fronts, one of k_dp_class_fronts up to 64 (as many as the profile's
+    dispatches per solve say), any other kernel's covers one."""
+    fronts = 1.0
+    if kernel == "k_dp_small":
+        fronts = float(max(1, L - 1))
+    elif kernel == "k_dp_class_fronts" and prof.get("calls") and prof.get("solves"):
+        fronts = (L - 1) / (prof["calls"] / prof["solves"])
+    per_launch = ("avg_us", "traffic_bytes", "lds_bytes", "fetch_bytes", "write_bytes")
+    return {k: v / fronts if k in per_launch and v is not None else v for k, v in prof.items()}, fronts
+
+
 def cpu_baseline(w, cfg_index, target_relax=3.0e10):
     """The oracle as it stands on a bounded sample of the same workload: the first instances
     one after the other on one core (about target_relax relaxations, at least one instance,
@@ -294,14 +307,7 @@ def main():
         key = f"{cfg_index}/{mode}" + (f"/groups{groups_forced}" if groups_forced else "") \
             + ("/perfront" if kernel == "k_dp_class" and args.fronts == 0 else "")
         prof = profile_of(kernel, (profiled.get("entries") or {}).get(key))
-        fronts_per_launch = 1.0
-        if kernel == "k_dp_class_fronts" and prof.get("calls") and prof.get("solves"):
-            # a launch of this kernel covers up to 64 layer fronts: the profile's per-dispatch
-            # figures are brought to one layer front (dispatches per solve / (L - 1))
-            fronts_per_launch = (w.L - 1) / (prof["calls"] / prof["solves"])
-            for name in ("avg_us", "traffic_bytes", "lds_bytes", "fetch_bytes", "write_bytes"):
-                if prof.get(name) is not None:
-                    prof[name] = prof[name] / fronts_per_launch
+        prof, fronts_per_launch = per_front(kernel, prof, w.L)
         common = {"kernel": kernel, "concurrent_launches": groups,
                   "layer_fronts_per_launch": fronts_per_launch,
                   "traffic": prof.get("traffic_bytes"),

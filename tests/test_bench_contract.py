@@ -31,6 +31,20 @@ def test_no_alu_fraction_without_a_count_and_no_counters_of_another_kernel():
     assert bench.profile_of("k_dp_bound", entry) == {} and bench.profile_of("k_dp_bound", None) == {}
 
 
+def test_profiled_figures_are_brought_to_one_front():
+    """The line's bytes and times are of a layer front; a launch of two kernels covers several."""
+    sys.path.insert(0, ROOT)
+    import bench
+    prof = dict(kernel="k", calls=20, solves=10, avg_us=46.0, traffic_bytes=92.0, lds_bytes=None)
+    assert bench.per_front("k_dp_small", prof, 24) == \
+        (dict(prof, avg_us=2.0, traffic_bytes=4.0), 23.0)
+    assert bench.per_front("k_dp_class_fronts", prof, 47) == \
+        (dict(prof, avg_us=2.0, traffic_bytes=4.0), 23.0)
+    assert bench.per_front("k_dp_push", prof, 24) == (prof, 1.0)
+    assert bench.per_front("k_dp_small", {}, 24) == ({}, 23.0)
+    assert prof["avg_us"] == 46.0
+
+
 def test_counters_of_other_sources_are_not_used(tmp_path):
     """A kernel that was rewritten keeps its name; its old bytes and durations are not its own."""
     sys.path.insert(0, ROOT)
