@@ -75,9 +75,9 @@ typedef enum {
                                             plans, bit for bit)                             */
 
 #define GSEARCH_FLAG_FORCE_PUSH 0x8u      /* testing/tuning: always the register-tiled push
-                                            kernel (flat four-instruction argmin)          */
+                                            kernel                                         */
 #define GSEARCH_FLAG_FORCE_TILE 0x10u     /* testing/tuning: always the LDS-staged kernel
-                                            with the two-level argmin                      */
+                                            (beyond 128 strategies its LDS-streamed form)  */
 #define GSEARCH_FLAG_NO_BIN_UNIT 0x20u    /* testing: do not rescale an instance whose memories
                                             share a divisor.  By default an instance is solved
                                             in its own bin unit g = gcd of the O[l][s] that fit
@@ -236,11 +236,12 @@ int gsearch_instance_groups(gsearch_ctx *ctx);
  * GSEARCH_<NAME IN CAPITALS> when it is created (the library reads the environment nowhere
  * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide, 4 bound:
  * general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
- * "jsplit" (waves per tile), "waves_per_block", "row_groups", "streams" (instance groups),
+ * "jsplit" (waves per tile), "waves_per_block", "row_groups" (push kernel, up to 48
+ * strategies: groups of 64 rows per wave, 1 or 2; more count as 2), "streams" (instance groups),
  * "fronts" (class kernel: layer fronts per launch, 2..64; 0 or 1: one launch per front; -1, the
  * default: 64 wherever that form can run and is the faster one, by the tiles with work that
- * earlier solves of the context counted; it can run from three layers up, with no forced instance groups, on a GPU whose eight XCDs take
- * workgroups in turn; 2 or more ask for it wherever it can run),
+ * earlier solves of the context counted; it can run from three layers up, with no forced instance
+ * groups, on a GPU whose eight XCDs take workgroups in turn; 2 or more ask for it wherever it can run),
  * "front_tiles" (that form: workgroups per instance and layer front, in eights; 0, the default: as
  * many as the fronts of earlier solves of the context had 64-row tiles with work, one per tile of
  * the budget at first.  Whatever the number, the results are the same: a solve whose fronts need

@@ -2108,7 +2108,7 @@ int tuned_sp_for(int S) {
 
 // The class kernel keeps only its own share of the strategies per wave, so it also exists
 // for 192 and 256 padded strategies (129..256 strategies: the paper's strategy space on 256
-// and 512 devices), where the general path is left with the pull-form fallback.
+// and 512 devices).
 int class_sp_for(int S) {
   const int t = tuned_sp_for(S);
   if (t) return t;

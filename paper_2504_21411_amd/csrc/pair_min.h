@@ -6,9 +6,9 @@
 namespace gs {
 
 // The fp32 bits of a sum in the upper word, the index of its source in the lower.  Sums lie
-// between +0 and +inf, so the pair read as a double is finite and not negative (its exponent is
-// 0x7f8 at most; what stands for NaN in a table is finite as well), and doubles order the pairs
-// by sum, then by index: ONE V_MIN_F64 keeps the least sum together with the lowest source that
+// between +0 and +inf (tables with other entries, NaN among them, are reported in the data status and
+// their results mean nothing), so the pair read as a double is finite and not negative (its exponent
+// is 0x7f8 at most), and doubles order the pairs by sum, then by index: ONE V_MIN_F64 keeps the least sum together with the lowest source that
 // attains it, where compare and two selects are three.
 typedef unsigned pair_t __attribute__((ext_vector_type(2)));
 

@@ -1786,7 +1786,7 @@ def test_one_launch_kernel_is_taken_where_it_is_the_faster(gs, B, S, M, flags, k
         assert ctx.gsearch_forward_kernel() == kernel
 
 
-@pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=4),
+@pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=2, jsplit=3),
                                    dict(kernel=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
 @pytest.mark.parametrize("S", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 40, 41, 44, 45, 48])
 def test_flat_argmin_of_pairs(gs, oracle_mod, S, knobs):
