@@ -18,6 +18,8 @@ one folder "calib".  Inside a run folder, one sub-folder per rocprofv3 pass, eac
     lds     --pmc SQ_INSTS_LDS_LOAD SQ_INSTS_LDS_STORE SQ_INSTS_LDS_ATOMIC
                   SQ_INSTS_LDS_LOAD_BANDWIDTH SQ_INSTS_LDS_STORE_BANDWIDTH
                   SQ_INSTS_LDS_ATOMIC_BANDWIDTH SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS
+    mfma    --pmc SQ_INSTS_VALU SQ_INSTS_MFMA SQ_VALU_MFMA_BUSY_CYCLES SQ_ACTIVE_INST_VALU
+                  SQ_BUSY_CU_CYCLES SQ_WAIT_ANY        (kernels that use the matrix cores)
 
 and "calib" holds copy_fetch / copy_write (bench.py --copy-calibration under FETCH_SIZE /
 WRITE_SIZE) and lds (bench.py --lds-calibration under the lds counter set).  Counters are
@@ -109,6 +111,7 @@ NAMES = {"0": "cfg0_single_decoder", "1": "cfg1_batch_decoder", "2": "cfg2_heter
 SHAPES = {"0": "B=1, L=24, S=12, M=256", "1": "B=64, L=48, S=44, M=2048", "2": "B=256, L=32, S=44, M=4096, K=4",
           "3": "B=8, L=128, S=96, M=16384", "4": "B=2048, L=32, S=24, M=2048"}
 SQ = "SQ_WAVES SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_INSTS_VALU SQ_INSTS_SALU SQ_WAIT_INST_ANY SQ_INSTS_SMEM SQ_INSTS_LDS"
+MFMA = "SQ_INSTS_VALU SQ_INSTS_MFMA SQ_VALU_MFMA_BUSY_CYCLES SQ_ACTIVE_INST_VALU SQ_BUSY_CU_CYCLES SQ_WAIT_ANY"
 LDS = "SQ_INSTS_LDS_LOAD SQ_INSTS_LDS_STORE SQ_INSTS_LDS_ATOMIC SQ_INSTS_LDS_LOAD_BANDWIDTH SQ_INSTS_LDS_STORE_BANDWIDTH SQ_INSTS_LDS_ATOMIC_BANDWIDTH SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS"
 
 
@@ -147,6 +150,8 @@ def write_markdown(d, folder, notes):
         out.append("    rocprofv3 --pmc WRITE_SIZE -d <dir>/write -o r -- <B> --steps 3")
         out.append(f"    rocprofv3 --pmc {SQ} -d <dir>/sq -o r -- <B> --steps 3")
         out.append(f"    rocprofv3 --pmc {LDS} -d <dir>/lds -o r -- <B> --steps 3")
+        if any("SQ_INSTS_MFMA" in e["counters"] for _, e in items):
+            out.append(f"    rocprofv3 --pmc {MFMA} -d <dir>/mfma -o r -- <B> --steps 3")
         out.append("    rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) -d <dir>/calib/copy_fetch -o c -- python3 bench.py --copy-calibration")
         out.append(f"    rocprofv3 --pmc <the LDS set> -d <dir>/calib/lds -o c -- python3 bench.py --lds-calibration\n")
         out.append("| run | kernel | calls | avg µs | min | max | HBM fetch MB | write MB | total MB | LDS MB | VALU wave-insts | SALU | SMEM | LDS insts | waves |")
@@ -242,7 +247,7 @@ def main():
         if solves:
             e["solves"] = solves[0]
         merged = {}
-        for sub in ("fetch", "write", "sq", "lds"):
+        for sub in ("fetch", "write", "sq", "lds", "mfma"):
             c = counters(os.path.join(folder, sub))
             hit = [k for k in c if short(k) == short(fk)]
             if hit:
