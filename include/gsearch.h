@@ -237,7 +237,7 @@ int gsearch_instance_groups(gsearch_ctx *ctx);
  * else) and keeps them per context.  Names: "kernel" (1 push, 2 tile, 3 wide, 4 bound:
  * general forward kernel), "small" (0/1: one-launch kernel for small instances never / wherever it fits),
  * "jsplit" (waves per tile), "waves_per_block", "row_groups" (push kernel, up to 48
- * strategies: groups of 64 rows per wave, 1 or 2; more count as 2), "streams" (instance groups),
+ * strategies: groups of 64 rows per wave, 1, 2 or, up to 8, 4; more count as the largest), "streams" (instance groups),
  * "fronts" (class kernel: layer fronts per launch, 2..64; 0 or 1: one launch per front; -1, the
  * default: 64 wherever that form can run and is the faster one, by the tiles with work that
  * earlier solves of the context counted; it can run from three layers up, with no forced instance

@@ -2193,22 +2193,13 @@ static void launch_push(const Shape &s, const Workspace &w, int l, const float *
                         void *bp_l, hipStream_t st) {
   int jsplit, wpb;
   push_launch_shape(s, jsplit, wpb);
-  // Row groups per wave share a column's scalar loads, its T and O and the loop; they cost
-  // registers.  Measured, 7 fronts, us at one / two groups, the order as push_by_instance says: S = 8
-  // 8064 tiles 85 / 76, 12600 tiles 100 / 85, 16384 143 / 131, 37888 262 / 220 (min-only 250 / 208); S = 16
-  // 11280 tiles 178 / 181, 16384 238 / 227, 16884 235 / 231 (min-only 244 / 229); beyond, by instance: S
-  // = 16 42210 652 / 681 (534 / 560), 65536 747 / 814, S = 24 24101 578 / 599 (500 / 523), 65536 1485 /
-  // 1542, S = 32 23475 799 / 822 (625 / 656); plain: S = 16 31300 471 / 461 (442 / 439), S = 24 31300 851 /
-  // 807 (683 / 654), 18760 421 / 416 (413 / 414), S = 32 15640 522 / 541 (461 / 479); S = 44 16380 968 /
-  // 1025.  The knob "row_groups" overrides (1 or 2).
+  // (the knob "row_groups" overrides)
   const long long tiles = (long long)((s.M + 1 + kWave - 1) / kWave) * s.Bc * jsplit;
   const bool by_instance = push_by_instance(4ll * s.Bc * s.S * s.pitch, s.B);
   int ru = s.tune.row_groups;
-  if (ru < 1) {
-    const bool two = SP <= 8    ? tiles >= 4096
-                     : SP <= 16 ? tiles >= 12288 && (tiles < 24576 || !by_instance)
-                                : SP <= 32 && tiles >= 24576 && !by_instance;
-    ru = two ? 2 : 1;
+  if (ru < 1) ru = push_row_groups(s.S, bp_l != nullptr, tiles, by_instance);
+  if constexpr (SP <= 8) {
+    if (ru >= 4) return launch_push_ru<SP, 4>(s, w, l, src, dst, bp_l, jsplit, wpb, by_instance, st);
   }
   if constexpr (SP <= 48) {
     if (ru >= 2) return launch_push_ru<SP, 2>(s, w, l, src, dst, bp_l, jsplit, wpb, by_instance, st);

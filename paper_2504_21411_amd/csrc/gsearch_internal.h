@@ -21,7 +21,7 @@ struct Tuning {
   int small = -1;          // 0 / 1: the one-launch kernel for small instances never / wherever it fits
   int jsplit = 0;          // waves per tile
   int waves_per_block = 0; // push kernel: waves per workgroup (1..4)
-  int row_groups = 0;      // push kernel: 64-row groups per wave (1 or 2)
+  int row_groups = 0;      // push kernel: 64-row groups per wave (1, 2, 4)
   int streams = 0;         // instance groups on parallel streams
   int fronts = -1;         // class kernel: layer fronts per launch, 2..64 (0, 1: one launch per
                            // front; -1: 64 wherever that form can run)

@@ -1,4 +1,5 @@
-// Numbering of the push kernel's workgroups: plain functions of integers, for host and device alike.
+// Numbering of the push kernel's workgroups and the rows a wave takes: plain functions of integers, for
+// host and device alike.
 #pragma once
 
 namespace gs {
@@ -54,6 +55,30 @@ constexpr long long push_workgroups(long long row_blocks, long long B, int jspli
 // bins, min-only 482 / 513.
 constexpr bool push_by_instance(long long plane_bytes, int B) {
   return plane_bytes >= (64ll << 20) && (B % 8 == 0 || (B >= 32 && 10 * (8 - B % 8) <= B));
+}
+
+// Groups of 64 rows per wave: they share a column's scalar loads, its T and O and the loop; they cost
+// registers.  Measured, 7 fronts, us at one / two groups, the order as push_by_instance says: S = 8
+// 8064 tiles 85 / 76, 12600 tiles 100 / 85, 16384 143 / 131, 37888 262 / 220 (min-only 250 / 208); S = 16
+// 11280 tiles 178 / 181, 16384 238 / 227, 16884 235 / 231 (min-only 244 / 229); beyond, by instance: S
+// = 16 42210 652 / 681 (534 / 560), 65536 747 / 814, S = 24 24101 578 / 599 (500 / 523), 65536 1485 /
+// 1542, S = 32 23475 799 / 822 (625 / 656); plain: S = 16 31300 471 / 461 (442 / 439), S = 24 31300 851 /
+// 807 (683 / 654), 18760 421 / 416 (413 / 414), S = 32 15640 522 / 541 (461 / 479); S = 44 16380 968 /
+// 1025.
+// With a few strategies a column is so short that four groups pay.  Whole searches, two / four: S = 1 14
+// K tiles 66 / 60, 79 K 308 / 233; S = 2 57 K 108 / 92, min-only 319 K (15 fronts) 1219 / 818; S = 3 8.8 K 88 /
+// 86, 54 K 311 / 261, min-only 106 K 290 / 228; S = 4 10 K 107 / 112, 15.5 K 160 / 154, 43 K 236 / 197, by
+// instance 255 K min-only 1150 / 1196; S = 6 22 K 318 / 324, min-only 16 K 180 / 176, 28 K 283 / 260.  Over
+// 164 random shapes of up to 8 strategies the groups picked take 1.010 times the best ones' time, two at
+// most 1.055.
+constexpr int push_row_groups(int S, bool with_bp, long long tiles, bool by_instance) {
+  if (S <= 3 && tiles >= 8192) return 4;
+  if (S == 4 && tiles >= 12288 && !by_instance) return 4;
+  if (S <= 6 && !with_bp && tiles >= 16384 && !by_instance) return 4;
+  const bool two = S <= 8    ? tiles >= 4096
+                   : S <= 16 ? tiles >= 12288 && (tiles < 24576 || !by_instance)
+                             : S <= 32 && tiles >= 24576 && !by_instance;
+  return two ? 2 : 1;
 }
 
 } // namespace gs

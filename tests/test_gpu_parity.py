@@ -1786,7 +1786,8 @@ def test_one_launch_kernel_is_taken_where_it_is_the_faster(gs, B, S, M, flags, k
         assert ctx.gsearch_forward_kernel() == kernel
 
 
-@pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=2, jsplit=3),
+@pytest.mark.parametrize("knobs", [dict(kernel=1), dict(kernel=1, row_groups=2), dict(kernel=1, row_groups=4),
+                                   dict(kernel=1, row_groups=2, jsplit=3),
                                    dict(kernel=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
 @pytest.mark.parametrize("S", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 40, 41, 44, 45, 48])
 def test_flat_argmin_of_pairs(gs, oracle_mod, S, knobs):
@@ -1824,10 +1825,11 @@ def test_flat_argmin_of_pairs(gs, oracle_mod, S, knobs):
 
 @pytest.mark.parametrize("flags", [0, 0x4])
 @pytest.mark.parametrize("shape", [(259, 3, 8, 8100), (70, 3, 8, 31000), (8, 3, 8, 65535), (72, 3, 24, 1000),
-                                   (9, 4, 12, 700), (259, 4, 12, 300)], ids=lambda t: "B%dL%dS%dM%d" % t)
+                                   (9, 4, 12, 700), (259, 4, 12, 300), (70, 4, 3, 8100), (259, 3, 1, 2100),
+                                   (9, 4, 6, 1500)], ids=lambda t: "B%dL%dS%dM%d" % t)
 def test_push_kernel_orders(gs, oracle_mod, shape, flags):
-    """Both numberings of the push kernel's workgroups (by instance from planes of 64 MB on) with one
-    and two row groups and slices of the targets: batches rounded up to a multiple of 8, row blocks
+    """Both numberings of the push kernel's workgroups (by instance from planes of 64 MB on) with one,
+    two and four row groups and slices of the targets: batches rounded up to a multiple of 8, row blocks
     rounded up to an odd number, budgets that end anywhere."""
     binding, runner = gs
     B, L, S, M = shape
@@ -1838,7 +1840,7 @@ def test_push_kernel_orders(gs, oracle_mod, shape, flags):
     with runner.make_context(w, flags=flags) as ctx:
         ctx.gsearch_set_knob("small", 0)
         ctx.gsearch_set_knob("kernel", 1)
-        for jsplit, rows in ((0, 0), (1, 1), (3, 2)):
+        for jsplit, rows in ((0, 0), (1, 1), (3, 2), (1, 4)):
             ctx.gsearch_set_knob("jsplit", jsplit)
             ctx.gsearch_set_knob("row_groups", rows)
             got = runner.to_numpy(runner.run_step(ctx, dw, backtrace="all"))

@@ -16,6 +16,7 @@ SOURCE = """
 extern "C" long long workgroups(long long rb, long long B, int js, int run) { return gs::push_workgroups(rb, B, js, run); }
 extern "C" int run_of(long long rb, int by) { return gs::push_run(rb, by != 0); }
 extern "C" int by_instance(long long bytes, int B) { return gs::push_by_instance(bytes, B); }
+extern "C" int row_groups(int S, int bp, long long tiles, int by) { return gs::push_row_groups(S, bp != 0, tiles, by != 0); }
 extern "C" void items(unsigned n, int js, int B, int run, int *out) {
   for (unsigned i = 0; i < n; ++i) {
     const gs::PushItem it = gs::push_item(i, js, B, run);
@@ -35,6 +36,7 @@ def order(tmp_path_factory):
     lib.workgroups.restype = ctypes.c_longlong
     lib.workgroups.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     lib.run_of.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    lib.row_groups.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int]
     lib.by_instance.argtypes = [ctypes.c_longlong, ctypes.c_int]
 
     def items(B, row_blocks, jsplit, by):
@@ -82,6 +84,21 @@ def test_few_working_row_blocks_use_all_compute_units(order, row_blocks, working
     work = ((it[:, 0] < 2048) & (it[:, 1] >= first) & (it[:, 1] < last)).astype(int)
     load = np.bincount(np.arange(len(work)) % 32, weights=work, minlength=32)
     assert load.max() <= 2 * load.mean()
+
+
+def test_row_groups_of_a_wave(order):
+    """Few strategies on many tiles take four (up to 1.5 times the speed of two), and no count asks for a
+    form that is not built: four up to 8 strategies, two up to 48."""
+    groups = order[0].row_groups
+    assert groups(3, 0, 215000, 1) == 4 and groups(3, 1, 54000, 0) == 4 and groups(1, 0, 8192, 0) == 4
+    assert groups(4, 1, 43000, 0) == 4 and groups(4, 0, 255000, 1) == 2
+    assert groups(6, 0, 28000, 0) == 4 and groups(6, 1, 28000, 0) == 2
+    assert groups(3, 0, 8191, 0) == 2 and groups(3, 0, 4095, 0) == 1
+    for S in range(1, 129):
+        for tiles in (1, 4096, 8192, 12288, 16384, 24576, 1 << 20):
+            for bp in (0, 1):
+                for by in (0, 1):
+                    assert groups(S, bp, tiles, by) in ((1, 2, 4) if S <= 8 else (1, 2) if S <= 48 else (1,))
 
 
 def test_which_batches_are_numbered_by_instance(order):
