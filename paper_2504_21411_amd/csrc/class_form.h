@@ -18,6 +18,14 @@ namespace gs {
 // each): the form picked takes 1.010 times the best one's time on average, the same over three thousand
 // shapes left out of the fit, and more than 1.1 times in one of 25.  (Always one launch per front: 1.22
 // times; always several, eight or four waves by the strategies alone: 1.11.)
+//
+// Beyond a load of 500 to 700 tiles, outside the fit, one launch per front: its workgroups fill the chip
+// evenly and stay full, the other form's wait for each other as before.  500 shapes of 60 to 2000
+// instances, several fronts at the better wave count / one launch, loads of 400 to 1000 and beyond: 16 to
+// 32 strategies 1.03 to 1.19 / 1.3 to 1.6, 48 to 96 0.92 to 1.14 / 1.12 to 1.35, 128 and more 1.03 to 1.14 /
+// 1.1 to 1.4; the form picked takes 1.010 times the best one's time, 1.012 over 400 shapes that the limits
+// were not chosen by, 1.028 by the costs alone (815 instances, 20 strategies, 51 tiles, 27 layers: 3084 ->
+// 1903 us).  Under eight layers the rule of gsearch_api.hip stays.
 struct ClassCosts {
   float launch, base, tile, base8, tile8, base4, tile4;
 };
@@ -72,10 +80,14 @@ struct ClassForm {
   bool pays;  // that form is to be taken
 };
 
+constexpr bool class_load_is_large(int B, int SP, float used) {
+  return (float)((B + 7) / 8) * used > (SP > 32 && SP <= 96 ? 700.f : 500.f);
+}
+
 constexpr ClassForm class_form(int B, int L, int SP, bool with_bp, float used) {
   const ClassTimes t = class_times(B, L, SP, with_bp, used);
   const int waves = SP > 128 || t.eight <= t.four ? 8 : 4;
-  return {waves, (waves == 8 ? t.eight : t.four) < t.single};
+  return {waves, (waves == 8 ? t.eight : t.four) < t.single && !class_load_is_large(B, SP, used)};
 }
 
 // The same while nothing is known about how many tiles have work: by the costs for four tenths to all
@@ -88,7 +100,8 @@ constexpr ClassForm class_form_unknown(int B, int L, int SP, bool with_bp, int t
     sum = {sum.single + t.single, sum.four + t.four, sum.eight + t.eight};
   }
   const int waves = SP > 128 || sum.eight <= sum.four ? 8 : 4;
-  return {waves, (waves == 8 ? sum.eight : sum.four) <= 1.1f * sum.single};
+  return {waves, (waves == 8 ? sum.eight : sum.four) <= 1.1f * sum.single &&
+                     !class_load_is_large(B, SP, 0.7f * (float)tiles)};
 }
 
 } // namespace gs
