@@ -12,7 +12,9 @@ namespace gs {
 //
 // run = 0: items by row block, then instance, dealt round-robin.
 // run > 0: an XCD takes the row blocks of one instance one after the other, so that the parts of a
-// cache line that two tiles store (the shifts are not aligned) meet in its L2.  Two things keep the
+// cache line that two tiles store (the shifts are not aligned) meet in its L2.  Counted, 2048 instances,
+// 24 strategies, 2048 bins, a front: writes of less than 64 bytes 637 -> 240 thousand of 6.3 million with
+// backpointers, 85 -> 53 of 4.7 million min-only; HBM bytes 687 -> 676 MB.  Two things keep the
 // XCDs and their compute units evenly loaded however the work is spread:
 //   - round r gives instance 8 r + (XCD + r) % 8 to an XCD: budgets that repeat every eight
 //     instances would otherwise fill one XCD with the large ones (512 instances, 24 strategies, 4096
